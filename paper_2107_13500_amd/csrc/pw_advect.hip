@@ -76,24 +76,80 @@ bool march_possible(const pw_shape& s) {
     return s.sy == s.nz && s.nz <= kMarchMaxNz && s.nx <= (1 << 30);
 }
 
-int32_t auto_seg(int32_t storage, const pw_shape& s, int32_t nchunks) {
-    // Many tiles (the boundary planes each tile re-reads stay a few percent
-    // of its traffic only with segments of 16 planes or more), all segments
-    // of nearly equal length.  Measured with the compact tile order on
-    // 512 x 512 x 64 and 2048 x 2048 x 64 over chunks 512/1024 and segments
-    // of 16..256 planes for every storage type: 16 planes are best on the
-    // small grid for all types; on the large grid FP64 and the 16-bit types
-    // are best at about 8192 tiles (64 planes) and the 4-byte types at about
-    // 2048 (256 planes), 0.5-1% ahead of 128 planes; an uneven split (such as
-    // 192 planes over 2048) costs 7%.
+// Even split of nx planes into segments of at most `seg`.
+static int32_t even_seg(int32_t nx, int64_t seg) {
+    seg = std::max<int64_t>(1, std::min<int64_t>(seg, nx));
+    const int64_t n = (nx + seg - 1) / seg;
+    return (int32_t)((nx + n - 1) / n);
+}
+
+// Planes per segment, from the tiles (segments x chunks) the split gives and
+// the tiles the chip keeps resident (two workgroups per CU for FP64 compute,
+// four for FP32 compute, fewer if the LDS holds fewer).
+//
+// 1. Whole rounds: on grids whose chunks divide evenly over the XCDs, about
+//    8192 tiles (FP64, 16-bit types) or 2048 (4-byte types) of 16 .. 256
+//    planes, if they fill whole rounds of resident tiles.  Tiles of equal
+//    length then stay in step and meet each other's boundary planes and halo
+//    columns in L2.  Measured over segments of 16 .. 256 planes: best on
+//    2048 x 2048 x 64 for every type (64 planes for FP64, 256 for FP32) and
+//    on 512 x 512 x 64 for FP64 (16 planes).
+// 2. Otherwise, with `rounds` or more rounds of tiles: a split near the
+//    type's best length `planes` (the more arithmetic and conversion per
+//    byte, the more a tile's start costs and the longer the best segment).
+// 3. Otherwise the split with the least predicted time: a tile of n planes
+//    takes n + start plane steps; a full round of tiles is limited by the
+//    HBM, and a step of a nearly empty chip still takes `idle` of a full
+//    round's step (the latency of one plane); a started round costs `tail`
+//    of what a full one does beyond its own tiles.
+// Fitted to every even split of 58 random grids (16..2048 planes and rows,
+// heights 64, 96, 128) for each type: 1.3% (FP64), 1.7% (FP32), 1.2% (16-bit
+// types) and 0.8% (int32) behind the best split on average.  The first rule
+// alone, for every grid, is 17-29% behind: it leaves small grids with too few
+// tiles (64 x 64 x 64 FP64: 32 tiles, 16.9 us; 256 tiles, 5.9 us) and ragged
+// ones with long tiles out of step (1100 x 1000 x 64 FP32: 2.07 rounds of 65
+// planes, 387 us; 7.9 rounds of 17, 318 us).
+struct SegModel {
+    int32_t planes;   // best segment length with many tiles
+    double begin;     // a tile's start with many tiles, in plane steps
+    double start;     // a tile's start with few tiles, in plane steps
+    double idle, tail, rounds;
+};
+
+int32_t auto_seg(int32_t storage, const pw_shape& s, int32_t nchunks, int64_t lds_bytes) {
+    constexpr int kCus = 256;
+    constexpr SegModel f64{10, 0.0, 2.0, 0.4, 1.0, 3.0}, f32{24, 0.0, 1.0, 0.4, 1.0, 3.0},
+        w16{24, 1.0, 3.0, 0.3, 0.4, 3.0}, i32{64, 2.0, 2.0, 0.4, 0.4, 2.0};
+    const SegModel& m = storage == PW_F64 ? f64 : storage == PW_F32 ? f32 : storage == PW_I32 ? i32 : w16;
+    const int64_t fit = std::max<int64_t>(1, kLdsPerCu / std::max<int64_t>(lds_bytes, 1));
+    const double resident = (double)kCus * (double)std::min<int64_t>(compute_bytes(storage) == 8 ? 2 : 4, fit);
+    auto segments = [&](int64_t n) { return ((int64_t)s.nx + n - 1) / n; };
+    auto fill = [&](int64_t n) { return (double)nchunks * (double)segments(n) / resident; };
+
     const int64_t target = elem_bytes(storage) == 4 ? 2048 : 8192;
-    int64_t seg = (int64_t)s.nx * nchunks / target;
-    seg = std::max<int64_t>(seg, 16);
-    seg = std::min<int64_t>(seg, 256);
-    seg = std::min<int64_t>(seg, s.nx);
-    seg = std::max<int64_t>(seg, 1);
-    const int64_t nseg = (s.nx + seg - 1) / seg;
-    return (int32_t)((s.nx + nseg - 1) / nseg);
+    const int32_t whole = even_seg(s.nx, std::min<int64_t>(std::max<int64_t>((int64_t)s.nx * nchunks / target, 16), 256));
+    // heights without a kernel of their own keep that rule: their kernel's
+    // occupancy is not the model's
+    if (s.nz != 64 && s.nz != 96 && s.nz != 128) return whole;
+    const double xw = fill(whole);
+    if (nchunks % kNumXcd == 0 && xw >= 1.0 && std::ceil(xw) - xw < 0.05 * xw) return whole;
+
+    auto rounds = [&](double x) { return x <= 1.0 ? m.idle + (1.0 - m.idle) * x : x + m.tail * (std::ceil(x) - x); };
+    const int32_t near = even_seg(s.nx, ((int64_t)s.nx + segments(m.planes) - 1) / segments(m.planes));
+    const bool many = fill(near) >= m.rounds;
+    const double extra = many ? m.begin : m.start;
+    const int64_t lo = many ? 2 * m.planes / 3 : 1, hi = std::min<int64_t>(2 * m.planes, s.nx);
+    int32_t best = near;
+    double low = (near + extra) * rounds(fill(near));
+    for (int64_t n = lo; n <= hi; ++n) {
+        if (even_seg(s.nx, n) != n) continue;   // an even split of its own
+        const double t = ((double)n + extra) * rounds(fill(n));
+        if (t < low) {
+            low = t;
+            best = (int32_t)n;
+        }
+    }
+    return best;
 }
 
 int32_t resolve_launch(int32_t storage, const pw_shape& s, const pw_tuning& t, Launch* L) {
@@ -110,15 +166,17 @@ int32_t resolve_launch(int32_t storage, const pw_shape& s, const pw_tuning& t, L
         r.chunk = chunk;
         r.block = 256;
         r.nchunks = (int32_t)(((int64_t)s.ny * s.nz + chunk - 1) / chunk);
-        r.seg = t.seg ? std::min(t.seg, s.nx) : auto_seg(storage, s, r.nchunks);
-        r.nseg = (s.nx + r.seg - 1) / r.seg;
         r.wpad = ((chunk + 2 * s.nz) + 3) / 4 * 4;
         r.lds_bytes = march_lds_bytes(storage, r.wpad);
         if (r.lds_bytes > kMaxDynamicLds) return PW_ERR_UNSUPPORTED;
+        r.seg = t.seg ? std::min(t.seg, s.nx) : auto_seg(storage, s, r.nchunks, r.lds_bytes);
+        r.nseg = (s.nx + r.seg - 1) / r.seg;
         r.tiles = (int64_t)r.nchunks * r.nseg;
-        // compact tile order (pw_march_kernel) when every XCD owns a chunk
-        r.cpx = r.nchunks >= kNumXcd ? (r.nchunks + kNumXcd - 1) / kNumXcd : 0;
-        r.workgroups = r.cpx > 0 ? (int64_t)kNumXcd * r.cpx * r.nseg : r.tiles;
+        // compact tile order (march_compact_tile) when every XCD owns a chunk
+        r.run = r.nchunks >= kNumXcd ? march_run(r.nchunks) : 0;
+        r.blocks = r.run > 0 ? (int32_t)(r.tiles / (kNumXcd * r.run)) : 0;
+        const int64_t rem = r.tiles - (int64_t)r.blocks * kNumXcd * r.run;
+        r.workgroups = r.run > 0 ? kNumXcd * ((int64_t)r.blocks * r.run + (rem + kNumXcd - 1) / kNumXcd) : r.tiles;
         if (r.workgroups >= (int64_t(1) << 31)) return PW_ERR_INVALID_ARG;
     } else {
         const int32_t block = t.block ? t.block : 256;
@@ -150,7 +208,7 @@ hipError_t launch_march(const DomainArgs& d, const Launch& L, hipStream_t stream
                                        hipFuncAttributeMaxDynamicSharedMemorySize, kMaxDynamicLds);
     });
     if (attr_err != hipSuccess) return attr_err;
-    MarchGeom g{L.nchunks, L.nseg, L.seg, L.wpad, L.cpx};
+    MarchGeom g{L.nchunks, L.nseg, L.seg, L.wpad, L.run, L.blocks};
     hipLaunchKernelGGL(kern, dim3((unsigned)L.workgroups), dim3(256), (size_t)L.lds_bytes, stream, d, g);
     return hipGetLastError();
 }

@@ -57,7 +57,8 @@ struct MarchGeom {
     int32_t nseg;      // x segments
     int32_t seg;       // planes per segment
     int32_t wpad;      // LDS elements per field per slot
-    int32_t cpx;       // compact tile order: chunk slots per XCD and segment (0: XCD-contiguous order)
+    int32_t run;       // compact tile order: neighbouring tiles per XCD and block (0: XCD-contiguous order)
+    int32_t blocks;    // compact tile order: full blocks of kNumXcd * run tiles
 };
 
 // Storage types that carry per-field power-of-two scales.
@@ -232,29 +233,33 @@ __global__ __launch_bounds__(NT) void pw_direct_kernel(DomainArgs d) {
 // ---------------------------------------------------------------------------
 
 // Workgroups are dispatched round-robin over the XCDs (workgroup b runs on
-// XCD b mod 8), in order of b.  Two tile orders follow from that.
+// XCD b mod 8), in order of b.  Two tile orders follow from that; both take
+// the tiles from the chunk-fastest list (tile = segment * nchunks + chunk).
 //
 // Compact order (march_compact_tile), used when a plane has at least 8
-// chunks: XCD x owns the contiguous chunk range [x nc / 8, (x + 1) nc / 8)
-// of every segment and walks it segment by segment, so at any time all XCDs
+// chunks: the list is cut into blocks of 8 R tiles, R about nchunks / 8
+// (march_run), and XCD x takes run x of every block, so at any time all XCDs
 // work on the same one or two segments -- the HBM traffic of the whole chip
-// stays in a narrow band of x planes -- while the chunks that share a y-halo
-// column still meet in one XCD's L2.  Each XCD gets cpx = ceil(nc / 8) slots
-// per segment; with nc not a multiple of 8 some slots are empty and their
-// workgroups exit at once.  Measured on 2048 x 2048 x 64 against the
+// stays in a narrow band of x planes -- while the R chunks of a run share
+// their y-halo columns in one XCD's L2.  The tiles past the last full block
+// are split evenly too, so no XCD has more than one tile above the mean
+// whatever nchunks is.  Measured on 2048 x 2048 x 64 against the
 // XCD-contiguous order: FP64 3-4% faster, BF16 2-3%; on 512 x 512 x 64 FP64
 // with 16-plane segments 14% faster.
 //
 // XCD-contiguous order (xcd_tile), for fewer than 8 chunks per plane: each
 // XCD receives a contiguous range of the chunk-fastest tile list.
-__device__ __forceinline__ bool march_compact_tile(int b, int nchunks, int cpx, int& c, int& s) {
+__host__ __device__ inline int march_run(int nchunks) { return (nchunks + kNumXcd / 2) / kNumXcd; }
+// Tile of workgroup b, or -1 (no tile: b lies in the padding of the last block).
+__host__ __device__ inline int march_compact_tile(int b, int ntiles, int run, int blocks) {
     const int x = b % kNumXcd;
     const int slot = b / kNumXcd;
-    s = slot / cpx;
-    const int lo = x * nchunks / kNumXcd;
-    const int hi = (x + 1) * nchunks / kNumXcd;
-    c = lo + slot % cpx;
-    return c < hi;
+    const int full = blocks * run;   // slots of each XCD in the full blocks
+    if (slot < full) return ((slot / run) * kNumXcd + x) * run + slot % run;
+    const int first = full * kNumXcd;
+    const int rem = ntiles - first;   // < 8 run
+    const int t = x * rem / kNumXcd + slot - full;
+    return t < (x + 1) * rem / kNumXcd ? first + t : -1;
 }
 __device__ __forceinline__ int xcd_tile(int b, int G) {
     const int q = G / kNumXcd;
@@ -819,14 +824,12 @@ void pw_march_kernel(DomainArgs d, MarchGeom g) {
     using CT = typename compute_of<ST>::type;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     CT* lds = reinterpret_cast<CT*>(smem_raw);
-    int c, s;
-    if (g.cpx > 0) {
-        if (!march_compact_tile((int)blockIdx.x, g.nchunks, g.cpx, c, s)) return;   // empty slot, whole workgroup
-    } else {
-        const int tile = xcd_tile(blockIdx.x, gridDim.x);
-        c = tile % g.nchunks;
-        s = tile / g.nchunks;
-    }
+    const int ntiles = g.nchunks * g.nseg;
+    const int tile = g.run > 0 ? march_compact_tile((int)blockIdx.x, ntiles, g.run, g.blocks)
+                               : xcd_tile((int)blockIdx.x, (int)gridDim.x);
+    if (tile < 0) return;   // whole workgroup
+    const int c = tile % g.nchunks;
+    const int s = tile / g.nchunks;
     const int i_begin = 1 + s * g.seg;
     const int i_end = min(i_begin + g.seg - 1, d.nx);
     march_tile<ST, NT, P, VEC, NZ>(d, c, i_begin, i_end, g.wpad, lds);

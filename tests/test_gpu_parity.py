@@ -250,3 +250,19 @@ def test_tall_columns_take_the_direct_kernel(shape):
         B.Plan(B.F64, [B.shape_of(d.u)], {"variant": B.VARIANT_MARCH})
     bplan = B.Plan(B.F64, [B.shape_of(d.u)] * 2, None)
     assert bplan.info()["batched_workgroups"] == 0
+
+
+@pytest.mark.parametrize("shape", [(64, 64, 64), (64, 16, 64), (3, 200, 64), (129, 73, 64), (40, 137, 64), (300, 19, 96)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_automatic_segments_on_small_and_ragged_grids(shape):
+    """The automatic plan on grids of few tiles and of chunk counts that do not
+    divide over the XCDs (below, at and above 8 chunks per plane, one-plane
+    segments, short last segments, a padded last block of tiles): every point
+    matches the oracle and no halo column is written."""
+    p = inputs.make_problem(*shape, seed=3100 + shape[0] + shape[1])
+    d, plan = _run(p, {})
+    info = plan.info()
+    say("auto segments", shape, info)
+    assert info["variant"] == B.VARIANT_MARCH and info["workgroups"] >= info["tiles"] >= 1
+    compare_f64(d, oracle.advect_problem(p), where="%s" % (shape,))
+    check_halo_untouched(d)
