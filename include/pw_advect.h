@@ -207,9 +207,9 @@ int32_t pw_plan_get_info(const pw_plan *plan, pw_plan_info *info);
                       not read).
      scales           host pointer or NULL; see pw_scales.
      stream           hipStream_t or NULL.
-   Pointers must be aligned to their element size (PW_ERR_ALIGNMENT); wider
-   vector loads are used when the bases are 16-byte aligned and nz and sx are
-   multiples of the vector width, scalar loads otherwise. */
+   Pointers must be aligned to their element size (PW_ERR_ALIGNMENT); heights
+   64, 96 and 128 run fastest when the bases are 16-byte aligned and sx is a
+   multiple of 16 bytes. */
 int32_t pw_advect(const pw_plan *plan,
                   const void *u, const void *v, const void *w,
                   void *su, void *sv, void *sw,

@@ -105,13 +105,15 @@ __device__ __forceinline__ bool aligned16(const void* p) { return (reinterpret_c
 
 // Which per-tile code paths a batched kernel carries.  Every path inlined
 // into the batched kernel counts towards its register allocation, so a
-// plan launches the narrowest kind its shapes allow:
-//   kFixedNz  vector loads, column heights 64 / 96 / 128 only;
-//   kVector   vector loads, any column height;
-//   kAny      also element-wise loads (shapes without vector alignment).
-// The vector kinds need every field pointer 16-byte aligned; a record that
-// is not is skipped and counted like a shape mismatch.
-enum BatchKind { kFixedNz = 0, kVector = 1, kAny = 2 };
+// plan launches the kind its shapes need:
+//   kFixedNz  column heights 64 / 96 / 128 only, every vector aligned;
+//   kClass0.. any heights of at most kHeightClass[kind - kClass0] and any
+//             element alignment: the one run-time-height path of the class of
+//             the tallest column.
+// If every shape allows aligned vectors (vec_shapes), every field pointer must
+// be 16-byte aligned; a record that is not is skipped and counted like a
+// shape mismatch.
+enum BatchKind { kFixedNz = 0, kClass0 = 1, kClass1 = 2, kClass2 = 3 };
 
 // gate: NULL, or a device word that must be nonzero for the launch to run
 // (the allocation-free entry point's table check); if it is zero, workgroup
@@ -188,13 +190,12 @@ __global__ __launch_bounds__(NT) void pw_batched_kernel(const BatchDomain* __res
         const DomainArgs d = domain_from<ST>(a, b);
         const int i_begin = 1 + s * b.seg;   // <= nx: (nseg - 1) * seg < nx
         const int i_end = min(i_begin + b.seg - 1, b.nx);
-        const bool vec = vec_shapes && aligned16(a.u) && aligned16(a.v) && aligned16(a.w) && aligned16(a.su) &&
+        const bool vec = aligned16(a.u) && aligned16(a.v) && aligned16(a.w) && aligned16(a.su) &&
                          aligned16(a.sv) && aligned16(a.sw);
-        if (KIND != kAny && !vec) {
+        if (vec_shapes && !vec) {
             if (threadIdx.x == 0 && local == 0) atomicAdd(errors, 1ull);
             continue;   // uniform over the workgroup
         }
-        const int wpad = round_up4(P + 2 * b.nz);
         // Short tiles leave less time to hide a plane's latency: FP64
         // compute (three LDS slots) keeps three planes in flight, and every
         // storage type takes the branch-free data movement, whose exact
@@ -202,12 +203,14 @@ __global__ __launch_bounds__(NT) void pw_batched_kernel(const BatchDomain* __res
         // the 384-domain batch: FP64 1.45 -> 1.22 ms, FP32 0.75 -> 0.64 ms).
         constexpr int D = march_slots<CT>() == 3 ? 3 : 2;
         constexpr bool X = true;
-        if (vec && b.nz == 64) march_tile<ST, NT, P, true, 64, D, X>(d, c, i_begin, i_end, wpad, lds);
-        else if (vec && b.nz == 96) march_tile<ST, NT, P, true, 96, D, X>(d, c, i_begin, i_end, wpad, lds);
-        else if (vec && b.nz == 128) march_tile<ST, NT, P, true, 128, D, X>(d, c, i_begin, i_end, wpad, lds);
-        else if constexpr (KIND != kFixedNz) {
-            if (vec) march_tile<ST, NT, P, true, 0, D>(d, c, i_begin, i_end, wpad, lds);
-            else if constexpr (KIND == kAny) march_tile<ST, NT, P, false, 0, D>(d, c, i_begin, i_end, wpad, lds);
+        if constexpr (KIND != kFixedNz) {
+            march_tile<ST, NT, P, -kHeightClass[KIND - kClass0], D, X>(d, c, i_begin, i_end, lds);
+        } else if (b.nz == 64) {
+            march_tile<ST, NT, P, 64, D, X>(d, c, i_begin, i_end, lds);
+        } else if (b.nz == 96) {
+            march_tile<ST, NT, P, 96, D, X>(d, c, i_begin, i_end, lds);
+        } else {
+            march_tile<ST, NT, P, 128, D, X>(d, c, i_begin, i_end, lds);
         }
     }
 }
@@ -409,8 +412,9 @@ template <typename ST, int P>
 int occupancy_kind(int32_t kind, int64_t lds_bytes) {
     switch (kind) {
         case kFixedNz: return occupancy_of<ST, P, kFixedNz>(lds_bytes);
-        case kVector: return occupancy_of<ST, P, kVector>(lds_bytes);
-        case kAny: return occupancy_of<ST, P, kAny>(lds_bytes);
+        case kClass0: return occupancy_of<ST, P, kClass0>(lds_bytes);
+        case kClass1: return occupancy_of<ST, P, kClass1>(lds_bytes);
+        case kClass2: return occupancy_of<ST, P, kClass2>(lds_bytes);
         default: return 0;
     }
 }
@@ -442,8 +446,9 @@ template <typename ST, int P>
 hipError_t dispatch_kind(int32_t kind, const BatchedLaunch& bl, const pw_domain_args* args, hipStream_t stream) {
     switch (kind) {
         case kFixedNz: return launch_batched<ST, P, kFixedNz>(bl, args, stream);
-        case kVector: return launch_batched<ST, P, kVector>(bl, args, stream);
-        case kAny: return launch_batched<ST, P, kAny>(bl, args, stream);
+        case kClass0: return launch_batched<ST, P, kClass0>(bl, args, stream);
+        case kClass1: return launch_batched<ST, P, kClass1>(bl, args, stream);
+        case kClass2: return launch_batched<ST, P, kClass2>(bl, args, stream);
         default: return hipErrorInvalidValue;
     }
 }
@@ -522,7 +527,6 @@ int32_t batched_launch_shape(int32_t storage, const pw_shape* shapes, int32_t n,
     // arithmetic per byte, gain from longer marches (measured on the
     // 384-domain batch: FP64 and FP32 fastest at 12-16 planes, BF16 at 48+)
     const int32_t seg_max = t.seg ? t.seg : (elem_bytes(storage) >= 4 ? 16 : 64);
-    const int64_t vw = 16 / elem_bytes(storage);
     int32_t nzmax = 0;
     int64_t tiles = 0;
     bool vec = true, fixed_nz = true;
@@ -533,23 +537,22 @@ int32_t batched_launch_shape(int32_t storage, const pw_shape* shapes, int32_t n,
         domain_tiles(s.nx, s.ny, s.nz, chunk, seg_max, &b);
         tiles += (int64_t)b.nchunks * b.nseg;
         nzmax = std::max(nzmax, s.nz);
-        if (s.nz % vw || s.sx % vw || s.sy % vw) vec = false;
-        fixed_nz = fixed_nz && (s.nz == 64 || s.nz == 96 || s.nz == 128);
+        vec = vec && vector_shape(storage, s);
+        fixed_nz = fixed_nz && compiled_height(s.nz);
     }
     Launch r{};
     r.variant = PW_VARIANT_MARCH;
     r.chunk = chunk;
     r.seg = seg_max;
     r.block = 256;
-    r.wpad = ((chunk + 2 * nzmax) + 3) / 4 * 4;
-    r.lds_bytes = march_lds_bytes(storage, r.wpad);
+    const int32_t k = vec && fixed_nz ? kFixedNz : kClass0 + height_class(nzmax);
+    r.lds_bytes = march_lds_bytes(storage, chunk, k == kFixedNz ? nzmax : -kHeightClass[k - kClass0]);
     if (r.lds_bytes > kMaxDynamicLds) return PW_ERR_UNSUPPORTED;
     r.tiles = tiles;
     int dev = 0, cus = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e != hipSuccess) return report_hip(e);
-    const int32_t k = !vec ? kAny : (fixed_nz ? kFixedNz : kVector);
     const int64_t by_lds = std::max<int64_t>(1, kLdsPerCu / std::max<int64_t>(r.lds_bytes, 1));
     int64_t per_cu = std::min<int64_t>(by_lds, 8);
     const int occ = batched_occupancy(storage, chunk, k, r.lds_bytes);
@@ -631,7 +634,7 @@ int32_t batched_plan_init(pw_plan* p) {
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(nullptr, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone) return PW_ERR_CAPTURE;
     Launch L{};
-    int32_t kind = kAny;
+    int32_t kind = kFixedNz;
     bool vec = false;
     int32_t rc = batched_launch_shape(p->storage, p->shapes.data(), p->ndomains, p->tuning, &L, &kind, &vec);
     if (rc != PW_OK) return rc;

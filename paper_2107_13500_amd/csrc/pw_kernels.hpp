@@ -11,11 +11,13 @@
 //         plane is [p0 - nz, p0 + P + nz) -- the chunk plus one column of y
 //         halo on each side -- so every input element crosses HBM about once.
 //         Two or three later planes are in flight in registers while a plane
-//         is computed.  With a compile-time column height every LDS offset is
-//         an immediate, the ring rotation is unrolled so slots and register
-//         sets are compile-time too, and each thread computes two consecutive
-//         levels, sharing their neighbour reads and storing both results with
-//         one vector store.
+//         is computed.  The ring rotation is unrolled so slots and register
+//         sets are compile-time, and each thread computes two consecutive
+//         points, sharing their neighbour reads and storing both results with
+//         one vector store.  With a compile-time column height every LDS
+//         offset is an immediate; for other heights the window's LDS pitch is
+//         that of a height class, so only the three rows j-1, j, j+1 need a
+//         base address of their own.
 #pragma once
 
 #include <type_traits>
@@ -25,6 +27,15 @@
 namespace pw {
 
 constexpr int kMarchMaxNz = 256;   // largest column the march variant accepts
+// Height classes of the march kernel for column heights without a kernel of
+// their own: the kernel of class H stages windows of up to P + 2 H elements.
+// The bounds are where one more load round per thread begins at P = 512 (84:
+// two rounds of 4-element vectors for FP32 compute, four of 2-element ones for
+// FP64 compute; 170: five for FP64 compute, and the largest window with four
+// FP32-compute workgroups per CU in LDS).
+constexpr int kHeightClass[3] = {84, 170, kMarchMaxNz};
+__host__ __device__ constexpr int height_class(int nz) { return nz <= kHeightClass[0] ? 0 : (nz <= kHeightClass[1] ? 1 : 2); }
+constexpr bool compiled_height(int nz) { return nz == 64 || nz == 96 || nz == 128; }
 constexpr int kLdsPerCu = 160 * 1024;           // gfx950 LDS per CU (and per workgroup)
 constexpr int kMaxDynamicLds = kLdsPerCu - 1024;   // leaves room for a kernel's small static LDS
 constexpr int kNumXcd = 8;         // MI355X: 8 accelerator complex dies, one L2 each
@@ -56,7 +67,6 @@ struct MarchGeom {
     int32_t nchunks;   // chunks of P points over the interior (j, k) run
     int32_t nseg;      // x segments
     int32_t seg;       // planes per segment
-    int32_t wpad;      // LDS elements per field per slot
     int32_t run;       // compact tile order: neighbouring tiles per XCD and block (0: XCD-contiguous order)
     int32_t blocks;    // compact tile order: full blocks of kNumXcd * run tiles
 };
@@ -82,28 +92,36 @@ __host__ __device__ inline void fold_coefficients(double tcx, double tcy, const 
     }
 }
 
-// One load of a Raw value (2, 4, 8 or 16 bytes) through a global pointer, as
-// a plain integer vector (HIP's vector structs cannot be assigned from an
-// address-space-qualified lvalue), copied bit for bit.
-template <typename Raw>
+// Vectors of N elements of type T that are only aligned to A bytes.
+template <typename T, int N, int A> struct vec_at;
+#define PW_VEC_AT(T, N, A) \
+    template <> struct vec_at<T, N, A> { typedef T type __attribute__((ext_vector_type(N), aligned(A))); };
+PW_VEC_AT(uint32_t, 4, 4)
+PW_VEC_AT(uint32_t, 4, 8)
+PW_VEC_AT(uint32_t, 4, 16)
+PW_VEC_AT(uint32_t, 2, 2)
+PW_VEC_AT(uint32_t, 2, 4)
+PW_VEC_AT(uint32_t, 2, 8)
+PW_VEC_AT(uint32_t, 1, 2)
+PW_VEC_AT(uint32_t, 1, 4)
+PW_VEC_AT(int32_t, 2, 4)
+PW_VEC_AT(int32_t, 2, 8)
+PW_VEC_AT(float, 2, 4)
+PW_VEC_AT(float, 2, 8)
+PW_VEC_AT(double, 2, 8)
+PW_VEC_AT(double, 2, 16)
+#undef PW_VEC_AT
+
+// One load of a Raw value (8 or 16 bytes, aligned to ALIGN bytes) through a
+// global pointer, as a plain integer vector (HIP's vector structs cannot be
+// assigned from an address-space-qualified lvalue), copied bit for bit.
+template <typename Raw, int ALIGN>
 __device__ __forceinline__ Raw load_global(global_ptr<const char> p) {
-    typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
-    typedef uint32_t u32x2v __attribute__((ext_vector_type(2)));
+    static_assert(sizeof(Raw) == 8 || sizeof(Raw) == 16, "8 or 16 bytes");
+    using V = typename vec_at<uint32_t, sizeof(Raw) / 4, ALIGN>::type;
+    const V x = *reinterpret_cast<global_ptr<const V>>(p);
     Raw r;
-    if constexpr (sizeof(Raw) == 16) {
-        const u32x4v x = *reinterpret_cast<global_ptr<const u32x4v>>(p);
-        __builtin_memcpy(&r, &x, 16);
-    } else if constexpr (sizeof(Raw) == 8) {
-        const u32x2v x = *reinterpret_cast<global_ptr<const u32x2v>>(p);
-        __builtin_memcpy(&r, &x, 8);
-    } else if constexpr (sizeof(Raw) == 4) {
-        const uint32_t x = *reinterpret_cast<global_ptr<const uint32_t>>(p);
-        __builtin_memcpy(&r, &x, 4);
-    } else {
-        static_assert(sizeof(Raw) == 2, "2, 4, 8 or 16 bytes");
-        const uint16_t x = *reinterpret_cast<global_ptr<const uint16_t>>(p);
-        __builtin_memcpy(&r, &x, 2);
-    }
+    __builtin_memcpy(&r, &x, sizeof(Raw));
     return r;
 }
 
@@ -121,28 +139,32 @@ __device__ __forceinline__ void store_out(global_ptr<ST> p, typename compute_of<
     }
 }
 
-// Two consecutive outputs p[0], p[1] with one store (p aligned to 2 elements).
+// Two consecutive outputs p[0], p[1] with one store (p aligned to ALIGN elements).
 // BF16 and FP16 pairs are rounded by one packed conversion (v_cvt_pk_bf16_f32,
 // v_cvt_pk_f16_f32: round to nearest even, as from_compute).
 typedef double f64x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-template <typename ST>
+template <typename ST, int ALIGN>
 __device__ __forceinline__ void store_pair(global_ptr<ST> p, typename compute_of<ST>::type a, typename compute_of<ST>::type b) {
+    constexpr int A = ALIGN * (int)sizeof(ST);
     if constexpr (std::is_same<ST, double>::value) {
-        __builtin_nontemporal_store(f64x2{a, b}, reinterpret_cast<global_ptr<f64x2>>(p));
+        using f64x2a = typename vec_at<double, 2, A>::type;
+        __builtin_nontemporal_store(f64x2a{a, b}, reinterpret_cast<global_ptr<f64x2a>>(p));
     } else if constexpr (std::is_same<ST, float>::value) {
-        __builtin_nontemporal_store(f32x2{a, b}, reinterpret_cast<global_ptr<f32x2>>(p));
+        using f32x2a = typename vec_at<float, 2, A>::type;
+        __builtin_nontemporal_store(f32x2a{a, b}, reinterpret_cast<global_ptr<f32x2a>>(p));
     } else if constexpr (std::is_same<ST, fx32_t>::value) {
-        typedef int32_t i32x2 __attribute__((ext_vector_type(2)));
+        using i32x2 = typename vec_at<int32_t, 2, A>::type;
         __builtin_nontemporal_store(i32x2{from_compute<ST>(a).v, from_compute<ST>(b).v}, reinterpret_cast<global_ptr<i32x2>>(p));
     } else if constexpr (std::is_same<ST, bf16_t>::value || std::is_same<ST, f16_t>::value) {
         using H2 = typename std::conditional<std::is_same<ST, bf16_t>::value, bf16x2, f16x2>::type;
         const H2 h = __builtin_convertvector(f32x2{a, b}, H2);
         uint32_t bits;
         __builtin_memcpy(&bits, &h, 4);
-        __builtin_nontemporal_store(bits, reinterpret_cast<global_ptr<uint32_t>>(p));
+        using u32a = typename vec_at<uint32_t, 1, A>::type;
+        __builtin_nontemporal_store(u32a(bits), reinterpret_cast<global_ptr<u32a>>(p));
     } else {
         // int16, the result of from_compute in fewer instructions: clamp to
         // the int16 range (NaN becomes -32768), then add 1.5 * 2^23.  The sum
@@ -158,7 +180,8 @@ __device__ __forceinline__ void store_pair(global_ptr<ST> p, typename compute_of
         const float rb = __builtin_fminf(__builtin_fmaxf(b, -32768.0f), 32767.0f) + kRoundOffset;
         // bytes 0, 1 of ra, then bytes 0, 1 of rb
         const uint32_t bits = __builtin_amdgcn_perm(__float_as_uint(rb), __float_as_uint(ra), 0x05040100u);
-        __builtin_nontemporal_store(bits, reinterpret_cast<global_ptr<uint32_t>>(p));
+        using u32a = typename vec_at<uint32_t, 1, A>::type;
+        __builtin_nontemporal_store(u32a(bits), reinterpret_cast<global_ptr<u32a>>(p));
     }
 }
 
@@ -275,9 +298,9 @@ struct LdsAcc {
     const CT* m;   // plane i-1 at the point's window index
     const CT* c;   // plane i
     const CT* p;   // plane i+1
-    int nz_rt, wp_rt;
+    int nz_rt;
     __device__ __forceinline__ int nz() const { return NZ > 0 ? NZ : nz_rt; }
-    __device__ __forceinline__ int wp() const { return NZ > 0 ? WPAD : wp_rt; }
+    __device__ __forceinline__ static constexpr int wp() { return WPAD; }
     template <int di> __device__ __forceinline__ const CT* sel() const {
         return di < 0 ? m : (di > 0 ? p : c);
     }
@@ -292,30 +315,27 @@ struct LdsAcc {
 constexpr int round_up4(int x) { return (x + 3) / 4 * 4; }
 constexpr int gcd_int(int a, int b) { return b == 0 ? a : gcd_int(b, a % b); }
 
-template <typename CT> struct vec2_of;
-template <> struct vec2_of<double> { using type = f64x2; };
-template <> struct vec2_of<float> { using type = f32x2; };
+// A two-element LDS block aligned to ALIGN elements.
+template <typename CT, int ALIGN> using lds_pair = vec_at<CT, 2, ALIGN * (int)sizeof(CT)>;
 
-// LDS reads for point O (0 or 1) of a pair of consecutive levels whose first
-// point sits at an even window index: every read is an aligned two-element
-// load (8 or 16 bytes per lane, so lanes at an 8- or 16-byte stride hit the
-// LDS banks without conflicts), and the two points' identical loads are
-// shared.
-template <typename CT, int NZ, int WPAD, int O>
+// LDS reads for point O (0 or 1) of a pair of consecutive points: every read
+// is a two-element block starting an even number of elements from the pair's
+// first point, and the two points' identical loads are shared.  With a
+// compile-time even height the pair's window index is even, so each block is
+// one aligned read (8 or 16 bytes per lane, so lanes at an 8- or 16-byte
+// stride hit the LDS banks without conflicts); ALIGN = 1 states that blocks
+// are only aligned to an element.
+template <typename CT, int WPAD, int ALIGN, int O>
 struct PairAcc {
-    // field F of plane i-1, i, i+1 at the pair's (even) window index
-    const CT* m[3];
-    const CT* c[3];
-    const CT* p[3];
-    template <int F, int di> __device__ __forceinline__ const CT* sel() const {
-        return di < 0 ? m[F] : (di > 0 ? p[F] : c[F]);
-    }
+    const CT* const* row;   // rows j-1, j, j+1 of slot 0, field u at the pair's window index
+    int sm, sc, sp;         // slots of planes i-1, i, i+1 (compile-time after inlining)
     template <int F, int dk, int dj, int di>
     __device__ __forceinline__ CT get() const {
         constexpr int e = O + dk;                              // -1 .. 2 from the pair start
-        constexpr int start = e < 0 ? -2 : (e >= 2 ? 2 : 0);   // aligned two-element block
-        using V2 = typename vec2_of<CT>::type;
-        const V2 val = *reinterpret_cast<const V2*>(sel<F, di>() + dj * NZ + start);
+        constexpr int start = e < 0 ? -2 : (e >= 2 ? 2 : 0);   // two-element block
+        using V2 = typename lds_pair<CT, ALIGN>::type;
+        const int slot = di < 0 ? sm : (di > 0 ? sp : sc);
+        const V2 val = *reinterpret_cast<const V2*>(row[dj + 1] + (3 * slot + F) * WPAD + start);
         return val[e - start];
     }
     template <int dk, int dj, int di> __device__ __forceinline__ CT u() const { return get<0, dk, dj, di>(); }
@@ -327,8 +347,8 @@ struct PairAcc {
 // three for FP64, whose larger slots would otherwise cost occupancy.
 template <typename CT> constexpr int march_slots() { return sizeof(CT) == 4 ? 4 : 3; }
 
-// The aligned two-level blocks a pair of levels reads: field F, row offset dj,
-// plane offset di, block b in {-2, 0, 2} levels from the pair's start.  The
+// The two-element blocks a pair of points reads: field F, row offset dj,
+// plane offset di, block b in {-2, 0, 2} elements from the pair's start.  The
 // stencil's reads (pw_point) per (field, dj, di) as a mask of level offsets
 // dk (bit 0: dk = -1, bit 1: dk = 0, bit 2: dk = +1); a read at dk touches
 // block -2 (dk = -1, first point), block 0 (every dk) and block 2 (dk = +1,
@@ -348,9 +368,8 @@ constexpr int pair_key(int F, int dj, int di, int b) { return ((F * 3 + dj + 1) 
 constexpr int pair_carry_key(int F, int dj, int b) { return (F * 3 + dj + 1) * 3 + b / 2 + 1; }
 
 // Pair reads from blocks already held in registers (indexed by pair_key).
-template <typename CT, int O>
+template <typename CT, typename V2, int O>
 struct CachedPairAcc {
-    using V2 = typename vec2_of<CT>::type;
     const V2* blk;
     template <int F, int dk, int dj, int di>
     __device__ __forceinline__ CT get() const {
@@ -366,40 +385,58 @@ struct CachedPairAcc {
 
 // One (chunk, segment) tile of the march: chunk c of the interior (j, k) run,
 // planes i_begin .. i_end.  Every thread of the workgroup must run it (it
-// holds barriers); `lds` must hold 3 * march_slots<CT>() * wpad compute-type
-// elements.
-// NZ > 0: the domain's nz equals NZ and wpad equals round_up4(P + 2 NZ).
-template <typename ST, int NT, int P, bool VEC, int NZ, int DIST = 2, bool FORCE_EXACT = false>
+// holds barriers); `lds` must hold 3 * march_slots<CT>() * march_wpad(P, NZ)
+// compute-type elements.
+//
+// NZ > 0: the domain's nz equals NZ, and every plane and the vectors in it are
+// aligned to 16 bytes.
+//
+// NZ < 0: any height up to -NZ (a height class), any element alignment.  A
+// window is a run of elements whatever the height, so it is still moved in
+// whole vectors, at element alignment (the hardware takes 8- and 16-byte
+// accesses at any dword for the same number of cache lines, 16-bit pairs at
+// any halfword); the last vector of a window that is no multiple of VW starts
+// early and overlaps the one before it.  A pair of points may straddle two
+// columns (odd heights), so both points select their bottom and top results,
+// and a last chunk of an odd number of points ends with a pair that starts one
+// point early (same values stored twice).
+constexpr int march_wpad(int p, int nz) { return round_up4(p + 2 * (nz > 0 ? nz : -nz)); }
+template <typename ST, int NT, int P, int NZ, int DIST = 2, bool FORCE_EXACT = false>
 struct MarchTile {
     using CT = typename compute_of<ST>::type;
     // Elements per load: as many as fill 16 bytes of LDS in the compute type,
     // so each lane's write of a converted vector is one conflict-free 16-byte
     // store (16-bit and int32 storage then load 8 bytes per lane).
-    static constexpr int VW = VEC ? int(16 / sizeof(CT)) : 1;
-    static constexpr int WMAX = P + 2 * (NZ > 0 ? NZ : kMarchMaxNz);      // largest window
-    static constexpr int NVR = (3 * (WMAX / VW) + NT - 1) / NT;           // load rounds per thread (3 fields)
+    static constexpr int VW = int(16 / sizeof(CT));
+    static constexpr int WPAD = march_wpad(P, NZ);                         // LDS elements per field and slot
+    static constexpr int NVR = (3 * (WPAD / VW) + NT - 1) / NT;            // load rounds per thread (3 fields)
     static constexpr int PPT = P / NT;                                     // points per thread
-    static constexpr bool PAIR = VEC && NZ > 0 && NZ % 2 == 0 && P % (2 * NT) == 0;
-    static constexpr int WPAD = NZ > 0 ? round_up4(P + 2 * NZ) : 0;
+    static constexpr bool RT = NZ < 0;                                     // run-time height, element alignment
+    static constexpr bool PAIR = P % (2 * NT) == 0;
+    static_assert(RT || NZ % 2 == 0, "pairs of levels need an even compiled height");
     // Branch-free data movement (see the constructor) where storage is
     // narrower than the compute type: those kernels are bound by instruction
     // issue, and exact load counting lets two planes stay in flight.  FP32
     // and FP64 storage are bound by HBM and keep the branches, which cost
     // fewer registers (measured: 4% faster for them, 4-23% slower for the
     // converting types).
-    static constexpr bool EXACT = NZ > 0 && (FORCE_EXACT || sizeof(ST) < sizeof(CT));
+    static constexpr bool EXACT = FORCE_EXACT || sizeof(ST) < sizeof(CT);
+    // points past the chunk's end repeat its last ones (below)
+    static constexpr bool CLAMP = EXACT || RT;
     static constexpr int NSLOT = march_slots<CT>();                       // planes in the LDS ring
-    static_assert(!VEC || VW * sizeof(ST) == 16 || VW * sizeof(ST) == 8, "8- or 16-byte loads");
-    using Raw = typename std::conditional<VEC, typename std::conditional<VW * sizeof(ST) == 16, uint4, uint2>::type,
-                                          ST>::type;
+    static_assert(VW * sizeof(ST) == 16 || VW * sizeof(ST) == 8, "8- or 16-byte loads");
+    using Raw = typename std::conditional<VW * sizeof(ST) == 16, uint4, uint2>::type;
+    static constexpr int RAW_ALIGN = RT ? int(sizeof(ST)) : int(sizeof(Raw));
+    static constexpr int PAIR_ALIGN = RT ? 1 : 2;   // elements a pair's window index is a multiple of
+    using V2 = typename lds_pair<CT, PAIR_ALIGN>::type;
     static_assert(P % NT == 0, "P must be a multiple of the block size");
 
     const DomainArgs& d;
     CT* lds;
-    int nz_rt, wpad_rt, wb, wlen, pend;
+    int nz_rt, wb, wlen, pend;
     int li[PPT];
     int kk[PPT];
-    bool live[PPT];          // point lies in the chunk (always true when EXACT)
+    bool live[PPT];          // point lies in the chunk (always true when CLAMP)
     CT hx[3], hy[3];       // uniform x and y coefficients of su, sv, sw
     CT zc[PPT][6];         // per-level vertical coefficients of each point
     // CARRY (with the branch-free data movement): blocks read at plane i as
@@ -410,7 +447,6 @@ struct MarchTile {
     // bound by HBM, measured 4% slower with it: the carried registers cost a
     // resident workgroup per CU.)
     static constexpr bool CARRY = PAIR && EXACT;
-    using V2 = typename vec2_of<CT>::type;
     V2 cm[CARRY ? PPT / 2 : 1][27];
     V2 c0[CARRY ? PPT / 2 : 1][27];
     // CARRY: the x-face sums of sv's and sw's x terms, carried from plane to
@@ -429,6 +465,9 @@ struct MarchTile {
     // coefficients xu, yu, yv, xv, xw, yw.
     static constexpr bool ZEND = CARRY && arith_of<ST>::type::kExactZeroFlux && is_fixed_point<ST>;
     CT ph[ZEND ? PPT : 1][6];
+    // Rows j-1, j, j+1 at each pair's window index in slot 0, field u: with a
+    // compile-time height one address and two immediates.
+    const CT* row[PAIR ? PPT / 2 : 1][3];
     // The window vectors of all three fields are spread over the workgroup:
     // round r of this thread moves vector t + r NT -- field fsel[r] (-1: none),
     // element pointer gp[r] into the window of the next plane to load, LDS
@@ -444,44 +483,42 @@ struct MarchTile {
     Raw st[DIST][NVR];
 
     __device__ __forceinline__ int nz() const { return NZ > 0 ? NZ : nz_rt; }
-    __device__ __forceinline__ int wpad() const { return NZ > 0 ? WPAD : wpad_rt; }
-    __device__ __forceinline__ int slot_elems() const { return 3 * wpad(); }
+    static constexpr int SLOT = 3 * WPAD;   // elements of one ring slot
 
-    __device__ __forceinline__ MarchTile(const DomainArgs& dd, int c, int wpad_in, CT* l)
-        : d(dd), lds(l), nz_rt(dd.nz), wpad_rt(wpad_in) {
+    __device__ __forceinline__ MarchTile(const DomainArgs& dd, int c, CT* l) : d(dd), lds(l), nz_rt(dd.nz) {
         const int n = nz();
-        const int p0 = n + c * P;                       // first point of the chunk (j >= 1)
+        int p0 = n + c * P;                             // first point of the chunk (j >= 1)
         pend = min(p0 + P, (d.ny + 1) * n);             // one past the last interior point
+        // a pair needs two points: a last chunk of one starts a point early
+        // (never the only chunk, which has at least nz >= 2)
+        if (RT && PAIR && pend - p0 == 1) --p0;
         wb = p0 - n;                                    // window start: one column of y halo
         wlen = min(P + 2 * n, (d.ny + 2) * n - wb);
-        const int nvec = wlen / VW;   // vectors per field (wlen is a multiple of VW)
+        const int nvec = (wlen + VW - 1) / VW;   // vectors per field (wlen >= 5 >= VW; NZ > 0: a multiple of VW)
 #pragma unroll
         for (int r = 0; r < NVR; ++r) {
-            // With a compile-time height the rounds fit the window exactly but
-            // for the last round's tail; those lanes wrap round and move a
+            // EXACT: the lanes past the window wrap round and move a
             // duplicate of an early vector (identical data to the same LDS
             // place), so loads and LDS writes need no branch and the compiler
             // can count outstanding loads exactly instead of waiting for all.
             const int v = EXACT ? ((int)threadIdx.x + r * NT) % (3 * nvec) : (int)threadIdx.x + r * NT;
             const int f = v < 3 * nvec ? v / nvec : -1;
-            const int q = (v - (f < 0 ? 0 : f) * nvec) * VW;
+            int q = (v - (f < 0 ? 0 : f) * nvec) * VW;
+            if (RT) q = f < 0 ? 0 : min(q, wlen - VW);
             fsel[r] = f;
             const ST* base = static_cast<const ST*>(f == 0 ? d.u : (f == 1 ? d.v : d.w));
             gp[r] = as_global(reinterpret_cast<const char*>(base + (wb + q)));   // plane 0
-            loff[r] = (f < 0 ? 0 : f) * wpad() + q;
+            loff[r] = (f < 0 ? 0 : f) * WPAD + q;
         }
 #pragma unroll
         for (int q = 0; q < PPT; ++q) {
             const int t = (int)threadIdx.x;
             int p = PAIR ? p0 + 2 * (t + NT * (q / 2)) + (q % 2) : p0 + t + NT * q;
-            live[q] = p < pend;
-            // EXACT: points past the chunk's end (last chunk of a domain)
+            // CLAMP: points past the chunk's end (last chunk of a domain)
             // recompute the chunk's last point or pair and store the
             // identical result again, so stores need no branch either.
-            if (EXACT && !live[q]) {
-                p = PAIR ? pend - 2 + (q % 2) : pend - 1;
-                live[q] = true;
-            }
+            if (CLAMP) p = PAIR ? min(p, pend - 2 + (q % 2)) : min(p, pend - 1);
+            live[q] = p < pend;
             kk[q] = p % n + 1;
             li[q] = p - wb;
             const PointCoefs<CT> c = point_coefs<ST>(d, live[q] ? kk[q] : 1);
@@ -492,6 +529,12 @@ struct MarchTile {
             zc[q][4] = c.z1w;
             zc[q][5] = c.z2w;
         }
+        if constexpr (PAIR) {
+#pragma unroll
+            for (int pq = 0; pq < PPT / 2; ++pq)
+#pragma unroll
+                for (int dj = -1; dj <= 1; ++dj) row[pq][dj + 1] = lds + li[2 * pq] + dj * n;
+        }
 #pragma unroll
         for (int f = 0; f < 3; ++f) {
             hx[f] = static_cast<CT>(d.cx[f]);
@@ -501,8 +544,9 @@ struct MarchTile {
 #pragma unroll
             for (int q = 0; q < PPT; ++q) {
                 const CT h[6] = {hx[0], hy[0], hy[1], hx[1], hx[2], hy[2]};
-                const bool bottom = q % 2 == 0 && kk[q] == 1;   // first level of a pair: odd k
-                const bool top = q % 2 == 1 && kk[q] == n;      // second level: even k
+                // even heights: the first level of a pair is odd, the second even
+                const bool bottom = (RT || q % 2 == 0) && kk[q] == 1;
+                const bool top = (RT || q % 2 == 1) && kk[q] == nz();
 #pragma unroll
                 for (int e = 0; e < 6; ++e) ph[q][e] = (bottom || (top && e >= 4)) ? CT(0) : h[e];
                 if (bottom) {
@@ -528,14 +572,14 @@ struct MarchTile {
         const int64_t ps = d.sx * (int64_t)sizeof(ST);   // uniform plane stride in bytes
 #pragma unroll
         for (int r = 0; r < NVR; ++r) {
-            if (EXACT || fsel[r] >= 0) dst[r] = load_global<Raw>(gp[r]);
+            if (EXACT || fsel[r] >= 0) dst[r] = load_global<Raw, RAW_ALIGN>(gp[r]);
             gp[r] += ps;
         }
     }
 
     // Convert staged values to the compute type and write them to a slot.
     __device__ __forceinline__ void put_from(const Raw* src, int sidx) {
-        CT* slot = lds + sidx * slot_elems();
+        CT* slot = lds + sidx * SLOT;
 #pragma unroll
         for (int r = 0; r < NVR; ++r) {
             if (EXACT || fsel[r] >= 0) {
@@ -545,7 +589,7 @@ struct MarchTile {
                 } cv;
                 cv.raw = src[r];
                 CT out[VW];
-                if constexpr (std::is_same<ST, bf16_t>::value && VEC) {
+                if constexpr (std::is_same<ST, bf16_t>::value) {
                     // a BF16 value is the upper half of its FP32 value: per
                     // 32-bit word, shift the low element up, mask the high one
                     uint32_t wd[sizeof(Raw) / 4];
@@ -559,23 +603,18 @@ struct MarchTile {
 #pragma unroll
                     for (int n = 0; n < VW; ++n) out[n] = to_compute(cv.e[n]);
                 }
-                CT* dst = slot + loff[r];
-                if constexpr (VW * sizeof(CT) >= 16) {
-#pragma unroll
-                    for (int n = 0; n < VW; n += 16 / (int)sizeof(CT)) {
-                        *reinterpret_cast<uint4*>(dst + n) = *reinterpret_cast<const uint4*>(out + n);
-                    }
-                } else {
-#pragma unroll
-                    for (int n = 0; n < VW; ++n) dst[n] = out[n];
-                }
+                static_assert(VW * sizeof(CT) == 16, "one 16-byte LDS write per vector");
+                using V4 = typename vec_at<uint32_t, 4, RT ? (int)sizeof(CT) : 16>::type;
+                V4 x;
+                __builtin_memcpy(&x, out, 16);
+                *reinterpret_cast<V4*>(slot + loff[r]) = x;
             }
         }
     }
 
-    // LDS address of field F of ring slot `slot` at pair pq's window index.
-    __device__ __forceinline__ const CT* block_base(int pq, int slot, int F) const {
-        return lds + slot * slot_elems() + F * WPAD + li[2 * pq];
+    // Block b of field F, row dj, of ring slot `slot` around pair pq.
+    __device__ __forceinline__ V2 lds_block(int pq, int slot, int F, int dj, int b) const {
+        return *reinterpret_cast<const V2*>(row[pq][dj + 1] + slot * SLOT + F * WPAD + b);
     }
 
     // CARRY: this step's blocks of pair pq, from the carried registers where
@@ -599,7 +638,7 @@ struct MarchTile {
                     blk[K] = c0[pq][pair_carry_key(F, dj, b)];
                 } else {
                     const int slot = di < 0 ? sm : (di > 0 ? sp : sc);
-                    blk[K] = *reinterpret_cast<const V2*>(block_base(pq, slot, F) + dj * NZ + b);
+                    blk[K] = lds_block(pq, slot, F, dj, b);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
@@ -625,9 +664,9 @@ struct MarchTile {
         if constexpr (K < 27) {
             constexpr int F = K / 9, dj = (K / 3) % 3 - 1, b = (K % 3 - 1) * 2;
             if constexpr (pair_block_used(F, dj, -1, b) && pair_block_used(F, dj, 0, b))
-                cm[pq][K] = *reinterpret_cast<const V2*>(block_base(pq, 0, F) + dj * NZ + b);
+                cm[pq][K] = lds_block(pq, 0, F, dj, b);
             if constexpr (pair_block_used(F, dj, 0, b) && pair_block_used(F, dj, 1, b))
-                c0[pq][K] = *reinterpret_cast<const V2*>(block_base(pq, 1, F) + dj * NZ + b);
+                c0[pq][K] = lds_block(pq, 1, F, dj, b);
             prime_blocks<K + 1>(pq);
         }
     }
@@ -649,7 +688,6 @@ struct MarchTile {
     // Compute plane i from the slots sm (plane i-1), sc (plane i), sp (plane i+1).
     __device__ __forceinline__ void compute(int i, int sm, int sc, int sp) {
         const int64_t obase = (int64_t)i * d.sx + wb;
-        const int se = slot_elems();
         using AR = typename arith_of<ST>::type;
         CT res[PPT][3];
         V2 blk[CARRY ? PPT / 2 : 1][81];   // CARRY: this step's blocks, indexed by pair_key
@@ -664,33 +702,26 @@ struct MarchTile {
             if constexpr (CARRY) {
                 if (q % 2 == 0) gather_blocks<0>(blk[q / 2], q / 2, sm, sc, sp);
                 if (q % 2 == 0) {
-                    CachedPairAcc<CT, 0> A{blk[q / 2]};
-                    pw_point<AR, false, !ZEND, false>(A, kk[q], nz(), c, res[q][0], res[q][1], res[q][2], xs[q]);
+                    CachedPairAcc<CT, V2, 0> A{blk[q / 2]};
+                    pw_point<AR, false, !ZEND, RT && !ZEND>(A, kk[q], nz(), c, res[q][0], res[q][1], res[q][2], xs[q]);
                 } else {
-                    CachedPairAcc<CT, 1> A{blk[q / 2]};
-                    pw_point<AR, false, false, !ZEND>(A, kk[q], nz(), c, res[q][0], res[q][1], res[q][2], xs[q]);
+                    CachedPairAcc<CT, V2, 1> A{blk[q / 2]};
+                    pw_point<AR, false, RT && !ZEND, !ZEND>(A, kk[q], nz(), c, res[q][0], res[q][1], res[q][2], xs[q]);
                     keep_blocks<0>(blk[q / 2], q / 2);
                 }
             } else if constexpr (PAIR) {
-                const CT *m[3], *cc[3], *pp[3];
-#pragma unroll
-                for (int f = 0; f < 3; ++f) {
-                    const int l0 = li[q & ~1];   // the pair's first (even) index
-                    m[f] = lds + sm * se + f * WPAD + l0;
-                    cc[f] = lds + sc * se + f * WPAD + l0;
-                    pp[f] = lds + sp * se + f * WPAD + l0;
-                }
-                // the pair's first level is odd (k = 1 possible, never the
-                // top); the second is even (never k = 1, the top possible)
+                // even heights: the pair's first level is odd (k = 1 possible,
+                // never the top); the second is even (never k = 1, the top
+                // possible)
                 if (q % 2 == 0) {
-                    PairAcc<CT, NZ, WPAD, 0> A{{m[0], m[1], m[2]}, {cc[0], cc[1], cc[2]}, {pp[0], pp[1], pp[2]}};
-                    pw_point<AR, false, true, false>(A, kk[q], nz(), c, res[q][0], res[q][1], res[q][2]);
+                    PairAcc<CT, WPAD, PAIR_ALIGN, 0> A{row[q / 2], sm, sc, sp};
+                    pw_point<AR, false, true, RT>(A, kk[q], nz(), c, res[q][0], res[q][1], res[q][2]);
                 } else {
-                    PairAcc<CT, NZ, WPAD, 1> A{{m[0], m[1], m[2]}, {cc[0], cc[1], cc[2]}, {pp[0], pp[1], pp[2]}};
-                    pw_point<AR, false, false, true>(A, kk[q], nz(), c, res[q][0], res[q][1], res[q][2]);
+                    PairAcc<CT, WPAD, PAIR_ALIGN, 1> A{row[q / 2], sm, sc, sp};
+                    pw_point<AR, false, RT, true>(A, kk[q], nz(), c, res[q][0], res[q][1], res[q][2]);
                 }
             } else {
-                LdsAcc<CT, NZ, WPAD> A{lds + sm * se + l, lds + sc * se + l, lds + sp * se + l, nz_rt, wpad()};
+                LdsAcc<CT, NZ, WPAD> A{lds + sm * SLOT + l, lds + sc * SLOT + l, lds + sp * SLOT + l, nz_rt};
                 pw_point<AR, false>(A, kk[q], nz(), c, res[q][0], res[q][1], res[q][2]);
             }
         }
@@ -699,14 +730,14 @@ struct MarchTile {
         if constexpr (PAIR) {
 #pragma unroll
             for (int q = 0; q < PPT; q += 2) {
-                if (!EXACT && !live[q]) continue;   // a pair never straddles the chunk end (P, nz even)
+                if (!CLAMP && !live[q]) continue;   // NZ > 0: a pair never straddles the chunk end (P, nz even)
 #pragma unroll
-                for (int f = 0; f < 3; ++f) store_pair(outs[f] + (uint32_t)li[q], res[q][f], res[q + 1][f]);
+                for (int f = 0; f < 3; ++f) store_pair<ST, PAIR_ALIGN>(outs[f] + (uint32_t)li[q], res[q][f], res[q + 1][f]);
             }
         } else {
 #pragma unroll
             for (int q = 0; q < PPT; ++q) {
-                if (!EXACT && !live[q]) continue;
+                if (!CLAMP && !live[q]) continue;
 #pragma unroll
                 for (int f = 0; f < 3; ++f) store_out(outs[f] + (uint32_t)li[q], res[q][f]);
             }
@@ -743,22 +774,6 @@ struct MarchTile {
         }
     }
 
-    // Run-time slots (any column height): DIST steps per iteration so the
-    // register sets stay compile-time.
-    template <int R>
-    __device__ __forceinline__ bool block_rt(int i, int i_end, int& sm, int& sc, int& sp) {
-        if constexpr (R == DIST) {
-            return true;
-        } else {
-            if (i + R > i_end) return false;
-            step<R>(i + R, i_end, sm, sc, sp);
-            sm = sc;
-            sc = sp;
-            sp = sp + 1 == NSLOT ? 0 : sp + 1;
-            return block_rt<R + 1>(i, i_end, sm, sc, sp);
-        }
-    }
-
     __device__ __forceinline__ void run(int i_begin, int i_end) {
         // the first planes are requested together, so a tile's start waits
         // for one memory latency, not several
@@ -787,25 +802,18 @@ struct MarchTile {
                 prime_sums(pq);
             }
         }
-        if constexpr (NZ > 0) {
-            for (int i = i_begin;; i += UNROLL) {
-                if (!block<0>(i, i_end)) break;
-            }
-        } else {
-            int sm = 0, sc = 1, sp = 2;
-            for (int i = i_begin;; i += DIST) {
-                if (!block_rt<0>(i, i_end, sm, sc, sp)) break;
-            }
+        for (int i = i_begin;; i += UNROLL) {
+            if (!block<0>(i, i_end)) break;
         }
         // the next tile of a persistent workgroup refills slots 0 and 1
         if constexpr (NSLOT == 4) __syncthreads();
     }
 };
 
-template <typename ST, int NT, int P, bool VEC, int NZ, int DIST = 2, bool FORCE_EXACT = false>
-__device__ __forceinline__ void march_tile(const DomainArgs& d, int c, int i_begin, int i_end, int wpad,
+template <typename ST, int NT, int P, int NZ, int DIST = 2, bool FORCE_EXACT = false>
+__device__ __forceinline__ void march_tile(const DomainArgs& d, int c, int i_begin, int i_end,
                                            typename compute_of<ST>::type* lds) {
-    MarchTile<ST, NT, P, VEC, NZ, DIST, FORCE_EXACT> t(d, c, wpad, lds);
+    MarchTile<ST, NT, P, NZ, DIST, FORCE_EXACT> t(d, c, lds);
     t.run(i_begin, i_end);
 }
 
@@ -818,7 +826,7 @@ __device__ __forceinline__ void march_tile(const DomainArgs& d, int c, int i_beg
 template <typename ST> constexpr int march_max_waves() { return std::is_same<ST, double>::value ? 2 : 8; }
 
 // Single domain: one workgroup per (chunk, segment) tile.
-template <typename ST, int NT, int P, bool VEC, int NZ>
+template <typename ST, int NT, int P, int NZ>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, march_max_waves<ST>())))
 void pw_march_kernel(DomainArgs d, MarchGeom g) {
     using CT = typename compute_of<ST>::type;
@@ -832,7 +840,7 @@ void pw_march_kernel(DomainArgs d, MarchGeom g) {
     const int s = tile / g.nchunks;
     const int i_begin = 1 + s * g.seg;
     const int i_end = min(i_begin + g.seg - 1, d.nx);
-    march_tile<ST, NT, P, VEC, NZ>(d, c, i_begin, i_end, g.wpad, lds);
+    march_tile<ST, NT, P, NZ>(d, c, i_begin, i_end, lds);
 }
 
 }  // namespace pw

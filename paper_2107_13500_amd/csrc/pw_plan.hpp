@@ -19,7 +19,6 @@ struct Launch {
     int32_t block = 0;     // threads per workgroup
     int32_t nchunks = 0;   // march: chunks per plane; direct: blocks per plane
     int32_t nseg = 0;      // march: segments; direct: planes
-    int32_t wpad = 0;      // march: LDS elements per field per slot
     int32_t run = 0;       // march: compact tile order, neighbouring tiles per XCD and block (0: not used)
     int32_t blocks = 0;    // march: compact tile order, full blocks of tiles
     int64_t workgroups = 0;
@@ -46,7 +45,7 @@ struct BatchState {
     const int32_t* d_order = nullptr;   // one workgroup per tile: each workgroup's tile (-1: none), or NULL
     int device = -1;
     bool vec_shapes = false;     // every shape allows 16-byte loads
-    int32_t kind = 2;            // code paths of the batched kernel (BatchKind in pw_batched.hip)
+    int32_t kind = 0;            // code paths of the batched kernel (BatchKind in pw_batched.hip)
 };
 
 }  // namespace pw
@@ -65,7 +64,8 @@ namespace pw {
 
 int64_t elem_bytes(int32_t storage);
 int64_t compute_bytes(int32_t storage);
-int64_t march_lds_bytes(int32_t storage, int32_t wpad);
+int32_t march_height(int32_t storage, const pw_shape& s);
+int64_t march_lds_bytes(int32_t storage, int32_t chunk, int32_t height);
 bool scaled_storage(int32_t storage);   // 16-bit and int32 types: per-field scales
 int32_t normalize_shape(const pw_shape& in, pw_shape* out);
 int64_t extent_elems(const pw_shape& s);
@@ -73,6 +73,7 @@ bool march_possible(const pw_shape& s);
 int32_t auto_seg(int32_t storage, const pw_shape& s, int32_t nchunks, int64_t lds_bytes);
 int32_t resolve_launch(int32_t storage, const pw_shape& s, const pw_tuning& t, Launch* L);
 bool any_overlap(const void* const ins[3], void* const outs[3], int64_t ext);
+bool vector_shape(int32_t storage, const pw_shape& s);   // every vector of 16-byte aligned arrays is aligned
 bool vector_ok(int32_t storage, const pw_shape& s, const void* const ins[3], void* const outs[3]);
 int32_t fill_domain_args(int32_t storage, const pw_shape& s, const void* u, const void* v, const void* w,
                          void* su, void* sv, void* sw, double tcx, double tcy, const double* tzc1,

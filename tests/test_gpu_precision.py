@@ -298,3 +298,45 @@ def test_fp32_storage_keeps_denormal_results(tuning):
         bound = 8 * 2.0 ** -149 + (UNIT_ROUNDOFF[B.F32] + FP32_ARITH) * m
         say("f32 denormal", name, tuning, "max %.3e err %.3e bound %.3e" % (m, err, bound))
         assert err <= bound, "%s: %.3e > %.3e" % (name, err, bound)
+
+
+@pytest.mark.parametrize("storage", [B.F64, B.F32, B.BF16, B.F16, B.I16, B.I32],
+                         ids=["f64", "f32", "bf16", "f16", "i16", "i32"])
+@pytest.mark.parametrize("shape", [(7, 1, 2), (3, 171, 3), (3, 27, 19), (4, 41, 25), (3, 12, 84), (3, 13, 85),
+                                   (2, 7, 170), (2, 5, 171), (2, 3, 255), (5, 9, 63)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_run_time_heights_agree_over_tilings(storage, shape):
+    """Heights without a kernel of their own: at the edges of the height
+    classes (84 / 85, 170 / 171, 255), odd heights (pairs of points straddle
+    columns, element-aligned vectors), windows that are no multiple of a
+    vector, last chunks of a single point (3 x 171, 27 x 19: 513; 41 x 25:
+    1025).  256-, 512- and 1024-point chunks run one point, one pair and two
+    pairs per thread on the same per-point arithmetic: bit-identical outputs,
+    within the arithmetic bound of the oracle, no halo column written."""
+    p = inputs.make_problem(*shape, seed=5200 + shape[1] + shape[2])
+    ins, outs = inputs.storage_scales(p, B.DTYPE_NAMES[storage])
+    sc = B.make_scales(ins, outs)
+    fields = [B.to_storage(a, storage, s, DEV) for a, s in zip((p.u, p.v, p.w), ins)]
+    c = p.coeffs
+    tz = [torch.from_numpy(x).to(DEV) for x in c.arrays()]
+    res = []
+    for chunk, seg in ((512, 2), (256, 1), (1024, 3), (0, 0)):
+        say("run-time height", B.DTYPE_NAMES[storage], shape, chunk, seg)
+        d = B.DeviceDomain(*fields, c.tcx, c.tcy, *tz, scales=sc)
+        for o in d.outputs:
+            o.fill_(-77)
+        d.run(B.Plan(storage, [B.shape_of(fields[0])], {"variant": B.VARIANT_MARCH, "chunk": chunk, "seg": seg}))
+        torch.cuda.synchronize()
+        for o in d.outputs:
+            assert all(bool((face == -77).all()) for face in (o[0], o[-1], o[:, 0], o[:, -1]))
+        res.append(d.outputs)
+    for other in res[1:]:
+        for a, b in zip(res[0], other):
+            assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+    deq = [B.from_storage(f, storage, s) for f, s in zip(fields, ins)]
+    ref = oracle.advect(*deq, c.tcx, c.tcy, *c.arrays())
+    for o, r, s in zip(res[0], ref, outs):
+        g = B.from_storage(o, storage, s)[1:-1, 1:-1]
+        m = np.max(np.abs(r[1:-1, 1:-1]))
+        bound = metrics.F64_PARITY_TOL if storage == B.F64 else (arith_bound(storage, s, m) if m > 0 else 0.0)
+        assert max_rel(g, r[1:-1, 1:-1]) <= bound
