@@ -97,7 +97,7 @@ enum { PW_F64 = 0, PW_F32 = 1, PW_BF16 = 2, PW_F16 = 3, PW_I16 = 4, PW_I32 = 5 }
 /* Kernel variants (pw_tuning.variant). */
 enum {
     PW_VARIANT_AUTO = 0,
-    PW_VARIANT_DIRECT = 1, /* one thread per point, every operand loaded through the caches */
+    PW_VARIANT_DIRECT = 1, /* any strides and heights (nx up to 65535): operands loaded through the caches */
     PW_VARIANT_MARCH = 2   /* workgroup stages y-z plane windows in LDS and marches along x */
 };
 

@@ -157,6 +157,30 @@ int32_t auto_seg(int32_t storage, const pw_shape& s, int32_t nchunks, int64_t ld
     return best;
 }
 
+// Default workgroup and planes per segment of the direct variant.  A wave
+// carries its planes from step to step, so segments only have to be long
+// enough to spread the two extra planes of their start, and short ones keep
+// neighbouring waves within reach of each other's rows in L1 and L2: 4 planes
+// for FP64 compute and 8 for FP32 compute are best or within 4% of the best
+// of 1, 2, 4, 8, 16, 32 on grids from 5 to 74 million points (250 x 310 x 60
+// padded FP64: 58 us with 4, 64 with 8, 77 with 1; 500 x 500 x 199 padded
+// BF16: 230 with 8, 234 with 4, 390 with 1), 2 on grids that do not fill the
+// chip (kWaves waves in flight).  FP64 compute on large grids takes
+// workgroups of 512 threads, whose eight waves share more rows (58 against
+// 61 us; 512 x 512 x 64: 181 against 195); the others 256.
+static int32_t direct_block(int32_t storage, const pw_shape& s) {
+    const int64_t pairs = (int64_t)s.ny * (((int64_t)s.nz + 1) / 2);
+    return compute_bytes(storage) == 8 && pairs * s.nx >= (int64_t(1) << 21) ? 512 : 256;
+}
+static int32_t direct_seg(int32_t storage, const pw_shape& s, int32_t nchunks, int32_t block) {
+    constexpr int64_t kWaves = 256 * 12;
+    const int64_t most = compute_bytes(storage) == 8 ? 4 : 8;
+    int64_t seg = (int64_t)nchunks * (block / 64) * s.nx / kWaves;
+    seg = std::max<int64_t>(2, std::min<int64_t>(seg, most));
+    while ((int64_t)nchunks * ((s.nx + seg - 1) / seg) >= (int64_t(1) << 30)) seg *= 2;   // the grid's limit
+    return even_seg(s.nx, seg);
+}
+
 int32_t resolve_launch(int32_t storage, const pw_shape& s, const pw_tuning& t, Launch* L) {
     Launch r{};
     int32_t variant = t.variant;
@@ -176,25 +200,27 @@ int32_t resolve_launch(int32_t storage, const pw_shape& s, const pw_tuning& t, L
         r.seg = t.seg ? std::min(t.seg, s.nx) : auto_seg(storage, s, r.nchunks, r.lds_bytes);
         r.nseg = (s.nx + r.seg - 1) / r.seg;
         r.tiles = (int64_t)r.nchunks * r.nseg;
-        // compact tile order (march_compact_tile) when every XCD owns a chunk
-        r.run = r.nchunks >= kNumXcd ? march_run(r.nchunks) : 0;
-        r.blocks = r.run > 0 ? (int32_t)(r.tiles / (kNumXcd * r.run)) : 0;
-        const int64_t rem = r.tiles - (int64_t)r.blocks * kNumXcd * r.run;
-        r.workgroups = r.run > 0 ? kNumXcd * ((int64_t)r.blocks * r.run + (rem + kNumXcd - 1) / kNumXcd) : r.tiles;
-        if (r.workgroups >= (int64_t(1) << 31)) return PW_ERR_INVALID_ARG;
     } else {
-        const int32_t block = t.block ? t.block : 256;
+        const int32_t block = t.block ? t.block : direct_block(storage, s);
         if (block != 64 && block != 128 && block != 256 && block != 512) return PW_ERR_INVALID_ARG;
-        if (s.nx > 65535) return PW_ERR_INVALID_ARG;   // x planes ride on grid.y
+        if (s.nx > 65535) return PW_ERR_INVALID_ARG;
         r.block = block;
         r.chunk = 0;
         r.seg = 1;
-        r.nchunks = (int32_t)(((int64_t)s.ny * s.nz + block - 1) / block);
-        r.nseg = s.nx;
-        r.workgroups = (int64_t)r.nchunks * s.nx;
+        const int64_t pairs = s.ny * (((int64_t)s.nz + 1) / 2);   // a lane takes two levels
+        const int64_t per = block / 64 * kDirectPairs;
+        r.nchunks = (int32_t)((pairs + per - 1) / per);
         r.lds_bytes = 0;
-        r.tiles = r.workgroups;
+        r.seg = direct_seg(storage, s, r.nchunks, block);
+        r.nseg = (s.nx + r.seg - 1) / r.seg;
     }
+    r.tiles = (int64_t)r.nchunks * r.nseg;
+    // compact tile order (march_compact_tile) when every XCD owns a chunk
+    r.run = r.nchunks >= kNumXcd ? march_run(r.nchunks) : 0;
+    r.blocks = r.run > 0 ? (int32_t)(r.tiles / (kNumXcd * r.run)) : 0;
+    const int64_t rem = r.tiles - (int64_t)r.blocks * kNumXcd * r.run;
+    r.workgroups = r.run > 0 ? kNumXcd * ((int64_t)r.blocks * r.run + (rem + kNumXcd - 1) / kNumXcd) : r.tiles;
+    if (r.workgroups >= (int64_t(1) << 31)) return PW_ERR_INVALID_ARG;
     *L = r;
     return PW_OK;
 }
@@ -231,14 +257,12 @@ hipError_t dispatch_march_p(const DomainArgs& d, const Launch& L, hipStream_t st
 
 template <typename ST>
 hipError_t launch_direct(const DomainArgs& d, const Launch& L, hipStream_t stream) {
-    dim3 grid((unsigned)L.nchunks, (unsigned)d.nx);
-    switch (L.block) {
-        case 64: hipLaunchKernelGGL((pw_direct_kernel<ST, 64>), grid, dim3(64), 0, stream, d); break;
-        case 128: hipLaunchKernelGGL((pw_direct_kernel<ST, 128>), grid, dim3(128), 0, stream, d); break;
-        case 256: hipLaunchKernelGGL((pw_direct_kernel<ST, 256>), grid, dim3(256), 0, stream, d); break;
-        case 512: hipLaunchKernelGGL((pw_direct_kernel<ST, 512>), grid, dim3(512), 0, stream, d); break;
-        default: return hipErrorInvalidValue;
-    }
+    const MarchGeom g{L.nchunks, L.nseg, L.seg, L.run, L.blocks};
+    const dim3 grid((unsigned)L.workgroups), block((unsigned)L.block);
+    const bool narrow = ((int64_t)d.ny + 2) * d.sy * (int64_t)sizeof(ST) < (int64_t(1) << 31);
+    if (!narrow) hipLaunchKernelGGL((pw_direct_kernel<ST, int64_t, true>), grid, block, 0, stream, d, g);
+    else if (d.nz % 2) hipLaunchKernelGGL((pw_direct_kernel<ST, uint32_t, true>), grid, block, 0, stream, d, g);
+    else hipLaunchKernelGGL((pw_direct_kernel<ST, uint32_t, false>), grid, block, 0, stream, d, g);
     return hipGetLastError();
 }
 

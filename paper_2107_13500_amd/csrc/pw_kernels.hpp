@@ -1,7 +1,8 @@
 // PW advection kernels for gfx950.
 //
-// direct  one thread per grid point; every operand is a global load, neighbour
-//         reuse is left to L1/L2.  Handles any strides; the correctness anchor.
+// direct  one lane per pair of levels, walking along x; every operand is a
+//         global load or a neighbouring lane's, the reuse of the rows j-1 and
+//         j+1 is left to L1/L2.  Handles any strides and heights.
 // march   the HBM-streaming kernel.  With packed columns (sy = nz) each x plane
 //         is one contiguous run of (ny + 2) * nz elements, so a workgroup owns a
 //         contiguous chunk of P points of that (j, k) run and walks along x.  It
@@ -214,44 +215,6 @@ __device__ __forceinline__ PointCoefs<typename compute_of<ST>::type> point_coefs
 }
 
 // ---------------------------------------------------------------------------
-// direct variant
-// ---------------------------------------------------------------------------
-template <typename ST>
-struct GAcc {
-    using CT = typename compute_of<ST>::type;
-    const ST* pu;
-    const ST* pv;
-    const ST* pw;
-    int64_t sy, sx;
-    template <int dk, int dj, int di>
-    __device__ __forceinline__ CT u() const { return to_compute(pu[dk + dj * sy + di * sx]); }
-    template <int dk, int dj, int di>
-    __device__ __forceinline__ CT v() const { return to_compute(pv[dk + dj * sy + di * sx]); }
-    template <int dk, int dj, int di>
-    __device__ __forceinline__ CT w() const { return to_compute(pw[dk + dj * sy + di * sx]); }
-};
-
-// grid: x over the ny*nz points of a plane in blocks of NT, y over x planes.
-template <typename ST, int NT>
-__global__ __launch_bounds__(NT) void pw_direct_kernel(DomainArgs d) {
-    using CT = typename compute_of<ST>::type;
-    const int g = blockIdx.x * NT + threadIdx.x;
-    if (g >= d.ny * d.nz) return;
-    const int k = g % d.nz + 1;
-    const int j = g / d.nz + 1;
-    const int i = blockIdx.y + 1;
-    const int64_t off = (int64_t)(k - 1) + (int64_t)j * d.sy + (int64_t)i * d.sx;
-    GAcc<ST> A{static_cast<const ST*>(d.u) + off, static_cast<const ST*>(d.v) + off,
-               static_cast<const ST*>(d.w) + off, d.sy, d.sx};
-    const PointCoefs<CT> c = point_coefs<ST>(d, k);
-    CT su, sv, sw;
-    pw_point<typename arith_of<ST>::type, true>(A, k, d.nz, c, su, sv, sw);
-    store_out(as_global(static_cast<ST*>(d.su) + off), su);
-    store_out(as_global(static_cast<ST*>(d.sv) + off), sv);
-    store_out(as_global(static_cast<ST*>(d.sw) + off), sw);
-}
-
-// ---------------------------------------------------------------------------
 // march variant
 // ---------------------------------------------------------------------------
 
@@ -381,6 +344,277 @@ struct CachedPairAcc {
     template <int dk, int dj, int di> __device__ __forceinline__ CT u() const { return get<0, dk, dj, di>(); }
     template <int dk, int dj, int di> __device__ __forceinline__ CT v() const { return get<1, dk, dj, di>(); }
     template <int dk, int dj, int di> __device__ __forceinline__ CT w() const { return get<2, dk, dj, di>(); }
+};
+
+// ---------------------------------------------------------------------------
+// direct variant
+// ---------------------------------------------------------------------------
+
+// One lane takes a pair of levels (2m + 1, 2m + 2) of a column and walks along
+// x through a segment of planes.  Nothing is staged in LDS: the pair's levels
+// in the rows j-1, j, j+1 of u, v, w are loaded once per plane (nine loads of
+// two levels) and kept in registers while the march needs them, at di = +1, 0
+// and -1; the level below the pair and the one above it come from the
+// neighbouring lanes (DPP wave shifts), so a wave computes 62 pairs and its
+// first and last lane only load.  The loads of the next step are issued before
+// the arithmetic of this one.  Bound by the vector memory instructions per
+// point and by the loads in flight (one plane per wave).
+//
+// OFF: type of a byte offset within a plane.  uint32_t (planes below 2 GiB):
+// buffer loads and stores off a scalar plane base, and lanes without a point
+// store at the end of the buffer (the plane), which the hardware drops, so no
+// branch hides the number of outstanding loads from the compiler.
+// ODD: columns of odd height; their last pair has one level (its loads start
+// one level early), and every level is stored by itself.
+template <typename ST, typename OFF, bool ODD>
+struct DirectPair {
+    using CT = typename compute_of<ST>::type;
+    using AR = typename arith_of<ST>::type;
+    using V2 = typename lds_pair<CT, 2>::type;
+    static constexpr bool NARROW = std::is_same<OFF, uint32_t>::value;
+    static constexpr int E = (int)sizeof(ST);
+    struct Raw {
+        ST e[2];
+    };
+    const DomainArgs& d;
+    OFF off[3];      // byte offset in a plane of the pair's loads in rows j-1, j, j+1
+    OFF out[2];      // byte offset of the stores (ODD: of each level; NARROW: beyond the plane if there is none)
+    bool live[2];    // the lane computes this level
+    bool one;        // ODD: the last pair, one level
+    int k0;          // the pair's first level
+    uint32_t bytes;  // NARROW: bytes of a plane
+    CT hx[3], hy[3], zc[2][6];
+    Raw raw[27];     // pairs of the next step by pair_carry_key(F, dj, 0)
+    V2 cm[27], c0[27];
+    CT xs[2][2];
+
+    // Plane offset at which a step first reads the pair of field F, row dj.
+    static constexpr int ahead(int F, int dj) { return pair_block_used(F, dj, 1, 0) ? 1 : 0; }
+
+    __device__ __forceinline__ DirectPair(const DomainArgs& dd, int64_t g, bool inner) : d(dd) {
+        const int pairs = (d.nz + 1) / 2;
+        const int64_t total = (int64_t)d.ny * pairs;
+        const bool in = inner && g >= 0 && g < total;
+        g = g < 0 ? 0 : (g < total ? g : total - 1);
+        const int j = (int)(g / pairs) + 1;
+        k0 = 2 * (int)(g % pairs) + 1;
+        one = ODD && k0 == d.nz;
+        const int lev = one ? k0 - 2 : k0 - 1;   // 0-based first level loaded
+#pragma unroll
+        for (int r = 0; r < 3; ++r) off[r] = (OFF)(((int64_t)(j + r - 1) * d.sy + lev) * E);
+        bytes = NARROW ? (uint32_t)(((int64_t)d.ny + 2) * d.sy * E) : 0u;
+        live[0] = in;
+        live[1] = in && !one;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            out[q] = (OFF)(((int64_t)j * d.sy + k0 - 1 + q) * E);
+            if (NARROW && !live[q]) out[q] = (OFF)bytes;
+        }
+#pragma unroll
+        for (int f = 0; f < 3; ++f) {
+            hx[f] = static_cast<CT>(d.cx[f]);
+            hy[f] = static_cast<CT>(d.cy[f]);
+        }
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const PointCoefs<CT> c = point_coefs<ST>(d, min(k0 + q, d.nz));
+            zc[q][0] = c.z1u;
+            zc[q][1] = c.z2u;
+            zc[q][2] = c.z1v;
+            zc[q][3] = c.z2v;
+            zc[q][4] = c.z1w;
+            zc[q][5] = c.z2w;
+        }
+    }
+
+    __device__ __forceinline__ int64_t plane_bytes(int i) const { return (int64_t)i * d.sx * E; }
+    __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer(void* f, int i) const {
+        constexpr int kRaw = 0x00027000;   // untyped, stride 0, no swizzle
+        return __builtin_amdgcn_make_buffer_rsrc(static_cast<char*>(f) + plane_bytes(i), 0, (int)bytes, kRaw);
+    }
+    template <int F, int dj>
+    __device__ __forceinline__ Raw load(int i) const {
+        Raw r;
+        const void* f = F == 0 ? d.u : (F == 1 ? d.v : d.w);
+        if constexpr (NARROW) {
+            const __amdgpu_buffer_rsrc_t b = buffer(const_cast<void*>(f), i);
+            if constexpr (E == 8) {
+                const auto x = __builtin_amdgcn_raw_buffer_load_b128(b, off[dj + 1], 0, 0);
+                __builtin_memcpy(&r, &x, 16);
+            } else if constexpr (E == 4) {
+                const auto x = __builtin_amdgcn_raw_buffer_load_b64(b, off[dj + 1], 0, 0);
+                __builtin_memcpy(&r, &x, 8);
+            } else {
+                const auto x = __builtin_amdgcn_raw_buffer_load_b32(b, off[dj + 1], 0, 0);
+                __builtin_memcpy(&r, &x, 4);
+            }
+        } else {
+            using V = typename vec_at<uint32_t, E == 2 ? 1 : 2 * E / 4, E>::type;
+            const V x = *reinterpret_cast<global_ptr<const V>>(as_global(static_cast<const char*>(f) + plane_bytes(i)) + off[dj + 1]);
+            __builtin_memcpy(&r, &x, sizeof(Raw));
+        }
+        return r;
+    }
+    // The pair in the compute type; the one level of a last odd pair comes first.
+    __device__ __forceinline__ V2 widen(const Raw& r) const {
+        const V2 v = V2{to_compute(r.e[0]), to_compute(r.e[1])};
+        return ODD && one ? V2{v[1], v[1]} : v;
+    }
+
+    // Value of the lane below (wave_shr:1) or above (wave_shl:1); the first
+    // and last lane, which have none, keep their own and do not store.
+    template <int CTRL>
+    static __device__ __forceinline__ float shift(float x) {
+        return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(x), __float_as_int(x), CTRL, 0xf, 0xf, false));
+    }
+    template <int CTRL>
+    static __device__ __forceinline__ double shift(double x) {
+        const uint64_t u = (uint64_t)__double_as_longlong(x);
+        const int lo = (int)(uint32_t)u, hi = (int)(uint32_t)(u >> 32);
+        const uint32_t a = (uint32_t)__builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xf, 0xf, false);
+        const uint32_t b = (uint32_t)__builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xf, 0xf, false);
+        return __longlong_as_double((long long)(((uint64_t)b << 32) | a));
+    }
+    // Block b of the pair whose own levels are v (only the level next to the
+    // pair is read of an outer block).
+    template <int b>
+    static __device__ __forceinline__ V2 outer(const V2& v) {
+        constexpr int kShr = 0x138, kShl = 0x130;
+        const CT x = b < 0 ? shift<kShr>(v[1]) : shift<kShl>(v[0]);
+        return V2{x, x};
+    }
+
+    // Issue the loads of step i.
+    template <int K>
+    __device__ __forceinline__ void load_step(int i) {
+        if constexpr (K < 9) {
+            constexpr int F = K / 3, dj = K % 3 - 1;
+            raw[pair_carry_key(F, dj, 0)] = load<F, dj>(i + ahead(F, dj));
+            load_step<K + 1>(i);
+        }
+    }
+    // This step's blocks, from the loads, the carried registers and the neighbouring lanes.
+    template <int K>
+    __device__ __forceinline__ void gather(V2* blk) const {
+        if constexpr (K < 54) {   // first the pairs themselves (b = 0), then the outer blocks
+            constexpr bool own = K < 27;
+            constexpr int F = (K % 27) / 9, dj = (K / 3) % 3 - 1, di = K % 3 - 1;
+            if constexpr (own && pair_block_used(F, dj, di, 0)) {
+                constexpr int key = pair_key(F, dj, di, 0);
+                static_assert(di != -1 || pair_block_used(F, dj, 0, 0), "a pair of plane i-1 that was not read at plane i-1");
+                if constexpr (di == ahead(F, dj)) blk[key] = widen(raw[pair_carry_key(F, dj, 0)]);
+                else blk[key] = di == -1 ? cm[pair_carry_key(F, dj, 0)] : c0[pair_carry_key(F, dj, 0)];
+            }
+            if constexpr (!own) {
+                if constexpr (pair_block_used(F, dj, di, -2)) gather_outer<F, dj, di, -2>(blk);
+                if constexpr (pair_block_used(F, dj, di, 2)) gather_outer<F, dj, di, 2>(blk);
+            }
+            gather<K + 1>(blk);
+        }
+    }
+    template <int F, int dj, int di, int b>
+    __device__ __forceinline__ void gather_outer(V2* blk) const {
+        constexpr int key = pair_key(F, dj, di, b);
+        if constexpr (di == -1) blk[key] = cm[pair_carry_key(F, dj, b)];
+        else if constexpr (di == 0 && pair_block_used(F, dj, 1, b)) blk[key] = c0[pair_carry_key(F, dj, b)];
+        else blk[key] = outer<b>(blk[pair_key(F, dj, di, 0)]);
+    }
+    // Keep this step's blocks that the next step reads again.
+    template <int K>
+    __device__ __forceinline__ void keep(const V2* blk) {
+        if constexpr (K < 27) {
+            constexpr int F = K / 9, dj = (K / 3) % 3 - 1, b = (K % 3 - 1) * 2;
+            if constexpr (pair_block_used(F, dj, -1, b)) cm[K] = blk[pair_key(F, dj, 0, b)];
+            if constexpr (pair_block_used(F, dj, 0, b) && pair_block_used(F, dj, 1, b)) c0[K] = blk[pair_key(F, dj, 1, b)];
+            keep<K + 1>(blk);
+        }
+    }
+    // Carried blocks before step i: planes i-1 and i.
+    template <int K>
+    __device__ __forceinline__ void prime(int i) {
+        if constexpr (K < 9) {
+            constexpr int F = K / 3, dj = K % 3 - 1;
+            constexpr int k0_ = pair_carry_key(F, dj, 0), km = pair_carry_key(F, dj, -2), kp = pair_carry_key(F, dj, 2);
+            if constexpr (pair_block_used(F, dj, -1, 0)) cm[k0_] = widen(load<F, dj>(i - 1));
+            if constexpr (ahead(F, dj) == 1) c0[k0_] = widen(load<F, dj>(i));
+            if constexpr (pair_block_used(F, dj, -1, -2)) cm[km] = outer<-2>(cm[k0_]);
+            if constexpr (pair_block_used(F, dj, -1, 2)) cm[kp] = outer<2>(cm[k0_]);
+            if constexpr (pair_block_used(F, dj, 0, -2) && pair_block_used(F, dj, 1, -2)) c0[km] = outer<-2>(c0[k0_]);
+            if constexpr (pair_block_used(F, dj, 0, 2) && pair_block_used(F, dj, 1, 2)) c0[kp] = outer<2>(c0[k0_]);
+            prime<K + 1>(i);
+        }
+    }
+
+    __device__ __forceinline__ void store(void* f, int i, CT a, CT b) const {
+        if constexpr (NARROW) {
+            constexpr int kNt = 2;   // non-temporal, as the march kernel's stores
+            const __amdgpu_buffer_rsrc_t r = buffer(f, i);
+            const Raw x{{from_compute<ST>(a), from_compute<ST>(b)}};
+            if constexpr (ODD) {
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    if constexpr (E == 8) {
+                        typename vec_at<uint32_t, 2, 8>::type w;
+                        __builtin_memcpy(&w, &x.e[q], 8);
+                        __builtin_amdgcn_raw_buffer_store_b64(w, r, out[q], 0, kNt);
+                    } else if constexpr (E == 4) {
+                        uint32_t w;
+                        __builtin_memcpy(&w, &x.e[q], 4);
+                        __builtin_amdgcn_raw_buffer_store_b32(w, r, out[q], 0, kNt);
+                    } else {
+                        uint16_t w;
+                        __builtin_memcpy(&w, &x.e[q], 2);
+                        __builtin_amdgcn_raw_buffer_store_b16(w, r, out[q], 0, kNt);
+                    }
+                }
+            } else if constexpr (E == 8) {
+                typename vec_at<uint32_t, 4, 16>::type w;
+                __builtin_memcpy(&w, &x, 16);
+                __builtin_amdgcn_raw_buffer_store_b128(w, r, out[0], 0, kNt);
+            } else if constexpr (E == 4) {
+                typename vec_at<uint32_t, 2, 8>::type w;
+                __builtin_memcpy(&w, &x, 8);
+                __builtin_amdgcn_raw_buffer_store_b64(w, r, out[0], 0, kNt);
+            } else {
+                uint32_t w;
+                __builtin_memcpy(&w, &x, 4);
+                __builtin_amdgcn_raw_buffer_store_b32(w, r, out[0], 0, kNt);
+            }
+        } else {
+            const auto p = as_global(static_cast<char*>(f) + plane_bytes(i));
+            if (live[0]) store_out<ST>(reinterpret_cast<global_ptr<ST>>(p + out[0]), a);
+            if (live[1]) store_out<ST>(reinterpret_cast<global_ptr<ST>>(p + out[1]), b);
+        }
+    }
+
+    __device__ __forceinline__ void run(int i_begin, int i_end) {
+        load_step<0>(i_begin);
+        prime<0>(i_begin);
+        const V2 a = cm[pair_carry_key(0, 0, 0)], up = cm[pair_carry_key(0, 0, 2)], r = cm[pair_carry_key(0, 1, 0)];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            xs[q][0] = a[q] + r[q];                      // u(k, j) + u(k, j+1) of plane i_begin - 1
+            xs[q][1] = a[q] + (q == 0 ? a[1] : up[0]);   // u(k) + u(k+1)
+        }
+        for (int i = i_begin; i <= i_end; ++i) {
+            V2 blk[81];
+            gather<0>(blk);
+            load_step<0>(min(i + 1, i_end));   // the last step loads again what it has: no branch, exact waits
+            CT res[2][3];
+            const PointCoefs<CT> c0q{hx[0], hy[0], zc[0][0], zc[0][1], hy[1], hx[1],
+                                     zc[0][2], zc[0][3], hx[2], hy[2], zc[0][4], zc[0][5]};
+            const PointCoefs<CT> c1q{hx[0], hy[0], zc[1][0], zc[1][1], hy[1], hx[1],
+                                     zc[1][2], zc[1][3], hx[2], hy[2], zc[1][4], zc[1][5]};
+            CachedPairAcc<CT, V2, 0> A{blk};
+            pw_point<AR, true, true, ODD>(A, k0, d.nz, c0q, res[0][0], res[0][1], res[0][2], xs[0]);
+            CachedPairAcc<CT, V2, 1> B{blk};
+            pw_point<AR, true, false, true>(B, k0 + 1, d.nz, c1q, res[1][0], res[1][1], res[1][2], xs[1]);
+            keep<0>(blk);
+            store(d.su, i, res[0][0], res[1][0]);
+            store(d.sv, i, res[0][1], res[1][1]);
+            store(d.sw, i, res[0][2], res[1][2]);
+        }
+    }
 };
 
 // One (chunk, segment) tile of the march: chunk c of the interior (j, k) run,
@@ -825,21 +1059,38 @@ __device__ __forceinline__ void march_tile(const DomainArgs& d, int c, int i_beg
 // not capped.
 template <typename ST> constexpr int march_max_waves() { return std::is_same<ST, double>::value ? 2 : 8; }
 
-// Single domain: one workgroup per (chunk, segment) tile.
+// Single domain: the (chunk, segment) tile of this workgroup, false if none.
+__device__ __forceinline__ bool single_tile(const MarchGeom& g, int nx, int& c, int& i_begin, int& i_end) {
+    const int tile = g.run > 0 ? march_compact_tile((int)blockIdx.x, g.nchunks * g.nseg, g.run, g.blocks)
+                               : xcd_tile((int)blockIdx.x, (int)gridDim.x);
+    if (tile < 0) return false;   // whole workgroup
+    c = tile % g.nchunks;
+    i_begin = 1 + tile / g.nchunks * g.seg;
+    i_end = min(i_begin + g.seg - 1, nx);
+    return true;
+}
+
+// Direct variant: 62 pairs of levels per wave, any workgroup of whole waves.
+constexpr int kDirectPairs = 62;
+template <typename ST, typename OFF, bool ODD>
+__global__ __launch_bounds__(512) void pw_direct_kernel(DomainArgs d, MarchGeom g) {
+    int c, i_begin, i_end;
+    if (!single_tile(g, d.nx, c, i_begin, i_end)) return;
+    const int waves = (int)blockDim.x / 64, wave = (int)threadIdx.x / 64, lane = (int)threadIdx.x % 64;
+    const int64_t first = ((int64_t)c * waves + wave) * kDirectPairs;
+    DirectPair<ST, OFF, ODD> p(d, first + lane - 1, lane >= 1 && lane <= kDirectPairs);
+    p.run(i_begin, i_end);
+}
+
+// March variant: one workgroup per (chunk, segment) tile.
 template <typename ST, int NT, int P, int NZ>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, march_max_waves<ST>())))
 void pw_march_kernel(DomainArgs d, MarchGeom g) {
     using CT = typename compute_of<ST>::type;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     CT* lds = reinterpret_cast<CT*>(smem_raw);
-    const int ntiles = g.nchunks * g.nseg;
-    const int tile = g.run > 0 ? march_compact_tile((int)blockIdx.x, ntiles, g.run, g.blocks)
-                               : xcd_tile((int)blockIdx.x, (int)gridDim.x);
-    if (tile < 0) return;   // whole workgroup
-    const int c = tile % g.nchunks;
-    const int s = tile / g.nchunks;
-    const int i_begin = 1 + s * g.seg;
-    const int i_end = min(i_begin + g.seg - 1, d.nx);
+    int c, i_begin, i_end;
+    if (!single_tile(g, d.nx, c, i_begin, i_end)) return;
     march_tile<ST, NT, P, NZ>(d, c, i_begin, i_end, lds);
 }
 

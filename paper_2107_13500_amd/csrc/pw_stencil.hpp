@@ -33,8 +33,8 @@
 //
 // `A` reads an input at a compile-time offset (dk, dj, di) from the point:
 //   A.template u<dk, dj, di>(), A.template v<...>(), A.template w<...>().
-// Offsets with dk = +1 are only requested when k < nz, dk = -1 only when
-// k >= 2, so no level outside 1..nz is ever read.
+// Every offset is read at every level; what A returns for a level outside
+// 1..nz is never used (but any value must be readable).
 #pragma once
 
 #include "pw_types.hpp"
@@ -150,16 +150,14 @@ struct PointCoefs {
     CT xw, yw, z1w, z2w;   // sw: tcx, tcy, tzd1(k), tzd2(k)
 };
 
-// GUARDED: reads above the column top only when k < nz (global-memory
-// accessors, where level nz+1 may lie outside the array).  Unguarded (LDS
-// windows, where every such read stays inside the staged window): all reads
-// are issued unconditionally and the column-top and k = 1 results are picked
-// by selects, so the code is straight-line and two points of one thread can
-// share their reads.  MAY_BOTTOM / MAY_TOP = false state that k is never 1 /
-// never nz for this point (known at compile time for pairs of levels in
-// even-height columns), which drops the corresponding select.
+// All reads are issued unconditionally and the column-top and k = 1 results
+// are picked by selects, so the code is straight-line and two points of one
+// thread can share their reads.  MAY_BOTTOM / MAY_TOP = false state that k is
+// never 1 / never nz for this point (known at compile time for pairs of
+// levels in even-height columns), which drops the corresponding select.
+// SELECT_TOP: the column top by a select for every policy (see kZeroTop).
 //
-// xs (unguarded form, policies with kCarrySums, or NULL): the x-face sums of
+// xs (policies with kCarrySums, or NULL): the x-face sums of
 // the x terms of sv and sw, carried along the x march.  The lower face of
 // plane i is the upper face of plane i-1, so on entry xs[0] holds
 // u(k, j, i-1) + u(k, j+1, i-1) (sv) and xs[1] holds u(k, j, i-1) +
@@ -167,18 +165,10 @@ struct PointCoefs {
 // the same operations on the same values as when formed here, so results do
 // not change.  (At the column top xs[1] leaves with the top-zeroed upper
 // value; only sw(nz) would read it, and that result is replaced by zero.)
-template <typename AR, bool GUARDED, bool MAY_BOTTOM = true, bool MAY_TOP = true, typename Acc,
+template <typename AR, bool SELECT_TOP, bool MAY_BOTTOM = true, bool MAY_TOP = true, typename Acc,
           typename CT = typename AR::T>
 __device__ __forceinline__ void pw_point(const Acc& A, int k, int nz, const PointCoefs<CT>& c, CT& su, CT& sv,
                                          CT& sw, CT* xs = nullptr) {
-    if constexpr (GUARDED) {
-        if (k < 2) {
-            su = CT(0);
-            sv = CT(0);
-            sw = CT(0);
-            return;
-        }
-    }
     const CT u0 = A.template u<0, 0, 0>();
     const CT v0 = A.template v<0, 0, 0>();
     const CT w0 = A.template w<0, 0, 0>();
@@ -200,7 +190,7 @@ __device__ __forceinline__ void pw_point(const Acc& A, int k, int nz, const Poin
     s = s + (c.yu * AR::kCrossScale) * AR::cross_flux(u_ym, v_ym, A.template v<0, -1, 1>(), u_yp, v0, v_xp);
     // sv: mirror of su, own-direction (y) term first
     CT t = c.yv * AR::self_flux(v_ym, v0, v_yp);
-    if constexpr (!GUARDED && AR::kCarrySums) {
+    if constexpr (AR::kCarrySums) {
         if (xs != nullptr) {
             const CT h = u0 + u_yp;   // upper x face of v, u(k, j, i) + u(k, j+1, i)
             t = t + (c.xv * AR::kCrossScale) * AR::cross_sums(v_xm, xs[0], v_xp, h);
@@ -222,7 +212,7 @@ __device__ __forceinline__ void pw_point(const Acc& A, int k, int nz, const Poin
         b = AR::add_vert(t, c.z1v, v_zm, w_zm, w_v_lo, c.z2v, v_zp, w0, w_yp);
         // sw: x and y terms with u, v summed over levels k, k+1; then w along z
         CT q;
-        if constexpr (!GUARDED && AR::kCarrySums) {
+        if constexpr (AR::kCarrySums) {
             if (xs != nullptr) {
                 const CT h = u0 + u_zp;   // upper x face of w, u(k, j, i) + u(k+1, j, i)
                 q = (c.xw * AR::kCrossScale) * AR::cross_sums(A.template w<0, 0, -1>(), xs[1], w_xp, h);
@@ -244,52 +234,41 @@ __device__ __forceinline__ void pw_point(const Acc& A, int k, int nz, const Poin
         a = s + c.z1u * u_zm * (w_zm + w_u_lo);
         b = t + c.z1v * v_zm * (w_zm + w_v_lo);
     };
-    if constexpr (GUARDED) {
-        if (k < nz) {
-            eval(A.template u<1, 0, 0>(), A.template v<1, 0, 0>(), A.template w<1, 0, 0>(), su, sv, sw);
-        } else {
-            top(su, sv);
-            sw = CT(0);
-        }
-    } else {
-        // every read is inside the staged window (level nz + 1 of a column is
-        // level 1 of the next one)
-        CT u_zp = A.template u<1, 0, 0>();
-        CT v_zp = A.template v<1, 0, 0>();
-        const CT w_zp = A.template w<1, 0, 0>();
-        const bool in = k < nz;
-        // FP32 compute (the VALU-bound 16-bit kernels): zero values above the
-        // top make the upper vertical fluxes exact zeros, the column-top form
-        // at no extra cost for finite inputs.  FP64 compute (HBM-bound) takes
-        // the column-top form by a select instead, which costs it nothing
-        // measurable and keeps the top results independent of the values
-        // above the top, finite or not.
-        constexpr bool kZeroTop = MAY_TOP && AR::kExactZeroFlux && sizeof(CT) == 4;
-        if constexpr (kZeroTop) {
-            u_zp = in ? u_zp : CT(0);
-            v_zp = in ? v_zp : CT(0);
-        }
-        CT fa, fb, fr;
-        eval(u_zp, v_zp, w_zp, fa, fb, fr);
-        if constexpr (MAY_TOP) {
-            if constexpr (!kZeroTop) {
-                CT ta, tb;
-                top(ta, tb);
-                fa = in ? fa : ta;
-                fb = in ? fb : tb;
-            }
-            fr = in ? fr : CT(0);
-        }
-        if constexpr (MAY_BOTTOM) {
-            const bool live = k >= 2;
-            fa = live ? fa : CT(0);
-            fb = live ? fb : CT(0);
-            fr = live ? fr : CT(0);
-        }
-        su = fa;
-        sv = fb;
-        sw = fr;
+    CT u_zp = A.template u<1, 0, 0>();
+    CT v_zp = A.template v<1, 0, 0>();
+    const CT w_zp = A.template w<1, 0, 0>();
+    const bool in = k < nz;
+    // FP32 compute (the VALU-bound 16-bit kernels): zero values above the
+    // top make the upper vertical fluxes exact zeros, the column-top form
+    // at no extra cost for finite inputs.  FP64 compute (HBM-bound) takes
+    // the column-top form by a select instead, which costs it nothing
+    // measurable and keeps the top results independent of the values
+    // above the top, finite or not.
+    constexpr bool kZeroTop = MAY_TOP && !SELECT_TOP && AR::kExactZeroFlux && sizeof(CT) == 4;
+    if constexpr (kZeroTop) {
+        u_zp = in ? u_zp : CT(0);
+        v_zp = in ? v_zp : CT(0);
     }
+    CT fa, fb, fr;
+    eval(u_zp, v_zp, w_zp, fa, fb, fr);
+    if constexpr (MAY_TOP) {
+        if constexpr (!kZeroTop) {
+            CT ta, tb;
+            top(ta, tb);
+            fa = in ? fa : ta;
+            fb = in ? fb : tb;
+        }
+        fr = in ? fr : CT(0);
+    }
+    if constexpr (MAY_BOTTOM) {
+        const bool live = k >= 2;
+        fa = live ? fa : CT(0);
+        fb = live ? fb : CT(0);
+        fr = live ? fr : CT(0);
+    }
+    su = fa;
+    sv = fb;
+    sw = fr;
 }
 
 }  // namespace pw

@@ -340,3 +340,83 @@ def test_run_time_heights_agree_over_tilings(storage, shape):
         m = np.max(np.abs(r[1:-1, 1:-1]))
         bound = metrics.F64_PARITY_TOL if storage == B.F64 else (arith_bound(storage, s, m) if m > 0 else 0.0)
         assert max_rel(g, r[1:-1, 1:-1]) <= bound
+
+
+@pytest.mark.parametrize("storage", [B.F64, B.F32, B.BF16, B.F16, B.I16, B.I32],
+                         ids=["f64", "f32", "bf16", "f16", "i16", "i32"])
+@pytest.mark.parametrize("shape,pad", [((1, 1, 2), 0), ((5, 1, 3), 1), ((4, 62, 2), 0), ((9, 4, 31), 5),
+                                       ((6, 3, 124), 4), ((3, 2, 257), 0), ((17, 37, 126), 2), ((2, 500, 5), 0)],
+                         ids=lambda s: str(s).replace(", ", "x"))
+def test_direct_kernel_on_any_strides(storage, shape, pad):
+    """The direct kernel at its edges: waves of 62 pairs that end inside, at and
+    past a column (62 x 2 levels, 124 levels, 31 levels), odd heights (a last
+    pair of one level), padded columns and planes, more and fewer waves than a
+    workgroup holds, every workgroup size: within the arithmetic bound of the
+    oracle, the same bits for every workgroup size, padding and halo columns
+    never written."""
+    nx, ny, nz = shape
+    p = inputs.make_problem(*shape, seed=6100 + nx + ny + nz)
+    ins, outs = inputs.storage_scales(p, B.DTYPE_NAMES[storage])
+    dt = B.torch_dtype(storage)
+    sy, sx = nz + pad, (ny + 2) * (nz + pad) + 3 * pad
+    c = p.coeffs
+    tz = [torch.from_numpy(x).to(DEV) for x in c.arrays()]
+    size = (nx + 1) * sx + (ny + 1) * sy + nz
+    first = None
+    for block in (64, 128, 256, 512, 0):
+        say("direct", B.DTYPE_NAMES[storage], shape, pad, block)
+        bufs = [torch.full((size,), -77, dtype=dt, device=DEV) for _ in range(6)]
+        v = [b.as_strided((nx + 2, ny + 2, nz), (sx, sy, 1)) for b in bufs]
+        for t, a, s in zip(v, (p.u, p.v, p.w), ins):
+            t.copy_(B.to_storage(a, storage, s, DEV))
+        plan = B.Plan(storage, [B.shape_of(v[0])], {"variant": B.VARIANT_DIRECT, "block": block})
+        B.advect(plan, *v, c.tcx, c.tcy, *tz, scales=B.make_scales(ins, outs))
+        torch.cuda.synchronize()
+        got = [t[1:-1, 1:-1].clone() for t in v[3:]]
+        for t in v[3:]:
+            t[1:-1, 1:-1] = -77
+        assert all(bool((b == -77).all()) for b in bufs[3:]), "written outside the interior columns"
+        if first is None:
+            first = got
+            deq = [B.from_storage(t, storage, s) for t, s in zip(v[:3], ins)]
+        for a, b in zip(first, got):
+            assert torch.equal(a.contiguous().view(torch.uint8), b.contiguous().view(torch.uint8))
+    ref = oracle.advect(*[np.ascontiguousarray(a) for a in deq], c.tcx, c.tcy, *c.arrays())
+    for t, r, s in zip(first, ref, outs):
+        g, r = B.from_storage(t, storage, s), r[1:-1, 1:-1]
+        m = np.max(np.abs(r))
+        bound = metrics.F64_PARITY_TOL if storage == B.F64 else (arith_bound(storage, s, m) if m > 0 else 0.0)
+        assert max_rel(g, r) <= bound
+        assert positive_zeros(g[:, :, 0])
+
+
+@pytest.mark.parametrize("nz", [4, 5])
+def test_direct_kernel_with_planes_beyond_two_gib(nz):
+    """Column pitches so large that an offset within a plane needs more than 32
+    bits (planes of 2 GiB and more take 64-bit offsets): the same bits as the
+    packed layout."""
+    nx, ny = 1, 1
+    p = inputs.make_problem(nx, ny, nz, seed=71)
+    sy = (1 << 30) // 3 + 16                    # int16: a plane of 3 columns spans 2 GiB
+    sx = 3 * sy
+    size = 2 * sx + 2 * sy + nz
+    ins, outs = inputs.storage_scales(p, "i16")
+    sc = B.make_scales(ins, outs)
+    c = p.coeffs
+    tz = [torch.from_numpy(x).to(DEV) for x in c.arrays()]
+    inp = torch.empty(size + 64, dtype=torch.int16, device=DEV)     # the inputs may share one buffer
+    res = [torch.empty(size, dtype=torch.int16, device=DEV) for _ in range(3)]
+    v = [inp[o:].as_strided((3, 3, nz), (sx, sy, 1)) for o in (0, 16, 32)]
+    o = [t.as_strided((3, 3, nz), (sx, sy, 1)) for t in res]
+    packed = [B.to_storage(a, B.I16, s, DEV) for a, s in zip((p.u, p.v, p.w), ins)]
+    for t, a in zip(v, packed):
+        t.copy_(a)
+    for t in o:
+        t.fill_(-77)
+    B.advect(B.Plan(B.I16, [B.shape_of(v[0])]), *v, *o, c.tcx, c.tcy, *tz, scales=sc)
+    d = B.DeviceDomain(*packed, c.tcx, c.tcy, *tz, scales=sc)
+    d.run(B.Plan(B.I16, [B.shape_of(packed[0])], {"variant": B.VARIANT_DIRECT}))
+    torch.cuda.synchronize()
+    for a, b in zip(o, d.outputs):
+        assert torch.equal(a[1:-1, 1:-1], b[1:-1, 1:-1])
+        assert bool((a[0] == -77).all()) and bool((a[2] == -77).all()) and bool((a[1, 0] == -77).all())
