@@ -228,9 +228,9 @@ int32_t resolve_launch(int32_t storage, const pw_shape& s, const pw_tuning& t, L
 // ---------------------------------------------------------------------------
 // launches
 // ---------------------------------------------------------------------------
-template <typename ST, int P, int NZ>
+template <typename ST, int P, int NZ, bool EVEN>
 hipError_t launch_march(const DomainArgs& d, const Launch& L, hipStream_t stream) {
-    auto kern = pw_march_kernel<ST, 256, P, NZ>;
+    auto kern = pw_march_kernel<ST, 256, P, NZ, EVEN>;
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
     std::call_once(once, [&] {
@@ -245,12 +245,12 @@ hipError_t launch_march(const DomainArgs& d, const Launch& L, hipStream_t stream
     return hipGetLastError();
 }
 
-template <typename ST, int NZ>
+template <typename ST, int NZ, bool EVEN>
 hipError_t dispatch_march_p(const DomainArgs& d, const Launch& L, hipStream_t stream) {
     switch (L.chunk) {
-        case 256: return launch_march<ST, 256, NZ>(d, L, stream);
-        case 512: return launch_march<ST, 512, NZ>(d, L, stream);
-        case 1024: return launch_march<ST, 1024, NZ>(d, L, stream);
+        case 256: return launch_march<ST, 256, NZ, EVEN>(d, L, stream);
+        case 512: return launch_march<ST, 512, NZ, EVEN>(d, L, stream);
+        case 1024: return launch_march<ST, 1024, NZ, EVEN>(d, L, stream);
         default: return hipErrorInvalidValue;
     }
 }
@@ -266,6 +266,15 @@ hipError_t launch_direct(const DomainArgs& d, const Launch& L, hipStream_t strea
     return hipGetLastError();
 }
 
+template <typename ST, bool EVEN>
+hipError_t launch_class(const DomainArgs& d, const Launch& L, hipStream_t stream) {
+    switch (height_class(d.nz)) {
+        case 0: return dispatch_march_p<ST, -kHeightClass[0], EVEN>(d, L, stream);
+        case 1: return dispatch_march_p<ST, -kHeightClass[1], EVEN>(d, L, stream);
+        default: return dispatch_march_p<ST, -kHeightClass[2], EVEN>(d, L, stream);
+    }
+}
+
 template <typename ST>
 hipError_t launch_typed(const DomainArgs& d, const Launch& L, bool vec, hipStream_t stream) {
     // Column heights 64 (the paper's and MONC's default), 96 and 128 get
@@ -274,23 +283,22 @@ hipError_t launch_typed(const DomainArgs& d, const Launch& L, bool vec, hipStrea
     // whose windows are moved in whole vectors and whose threads take pairs of
     // points too.  Against the kernel they had before (one point per thread,
     // every LDS address computed, element loads for odd heights or
-    // alignments): 300 x 420 x 80 FP64 131 -> 104 us (4.7 TB/s algorithmic),
+    // alignments): 300 x 420 x 80 FP64 131 -> 93 us (5.2 TB/s algorithmic),
     // 257 x 391 x 63 FP32 57 -> 34 us (4.4 TB/s), 160 x 180 x 165 BF16
-    // 59 -> 24 us.
+    // 59 -> 24 us.  Even heights have kernels of their own, whose LDS reads
+    // are aligned pairs (300 x 420 x 80 FP64 101 -> 93 us, BF16 38 -> 29 us
+    // against the kernel for any height, whose 4-byte reads at an 8-byte
+    // stride conflict in the banks).
     if (L.variant == PW_VARIANT_MARCH) {
         if (vec) {
             switch (d.nz) {
-                case 64: return dispatch_march_p<ST, 64>(d, L, stream);
-                case 96: return dispatch_march_p<ST, 96>(d, L, stream);
-                case 128: return dispatch_march_p<ST, 128>(d, L, stream);
+                case 64: return dispatch_march_p<ST, 64, true>(d, L, stream);
+                case 96: return dispatch_march_p<ST, 96, true>(d, L, stream);
+                case 128: return dispatch_march_p<ST, 128, true>(d, L, stream);
                 default: break;
             }
         }
-        switch (height_class(d.nz)) {
-            case 0: return dispatch_march_p<ST, -kHeightClass[0]>(d, L, stream);
-            case 1: return dispatch_march_p<ST, -kHeightClass[1]>(d, L, stream);
-            default: return dispatch_march_p<ST, -kHeightClass[2]>(d, L, stream);
-        }
+        return d.nz % 2 == 0 ? launch_class<ST, true>(d, L, stream) : launch_class<ST, false>(d, L, stream);
     }
     return launch_direct<ST>(d, L, stream);
 }

@@ -107,13 +107,15 @@ __device__ __forceinline__ bool aligned16(const void* p) { return (reinterpret_c
 // into the batched kernel counts towards its register allocation, so a
 // plan launches the kind its shapes need:
 //   kFixedNz  column heights 64 / 96 / 128 only, every vector aligned;
-//   kClass0.. any heights of at most kHeightClass[kind - kClass0] and any
+//   kEven0..  even heights of at most kHeightClass[kind - kEven0] and any
 //             element alignment: the one run-time-height path of the class of
-//             the tallest column.
+//             the tallest column;
+//   kClass0.. likewise for any heights.
 // If every shape allows aligned vectors (vec_shapes), every field pointer must
 // be 16-byte aligned; a record that is not is skipped and counted like a
 // shape mismatch.
-enum BatchKind { kFixedNz = 0, kClass0 = 1, kClass1 = 2, kClass2 = 3 };
+enum BatchKind { kFixedNz = 0, kEven0 = 1, kEven1 = 2, kEven2 = 3, kClass0 = 4, kClass1 = 5, kClass2 = 6 };
+constexpr int kind_class(int kind) { return kind >= kClass0 ? kind - kClass0 : kind - kEven0; }
 
 // gate: NULL, or a device word that must be nonzero for the launch to run
 // (the allocation-free entry point's table check); if it is zero, workgroup
@@ -204,13 +206,13 @@ __global__ __launch_bounds__(NT) void pw_batched_kernel(const BatchDomain* __res
         constexpr int D = march_slots<CT>() == 3 ? 3 : 2;
         constexpr bool X = true;
         if constexpr (KIND != kFixedNz) {
-            march_tile<ST, NT, P, -kHeightClass[KIND - kClass0], D, X>(d, c, i_begin, i_end, lds);
+            march_tile<ST, NT, P, -kHeightClass[kind_class(KIND)], (KIND < kClass0), D, X>(d, c, i_begin, i_end, lds);
         } else if (b.nz == 64) {
-            march_tile<ST, NT, P, 64, D, X>(d, c, i_begin, i_end, lds);
+            march_tile<ST, NT, P, 64, true, D, X>(d, c, i_begin, i_end, lds);
         } else if (b.nz == 96) {
-            march_tile<ST, NT, P, 96, D, X>(d, c, i_begin, i_end, lds);
+            march_tile<ST, NT, P, 96, true, D, X>(d, c, i_begin, i_end, lds);
         } else {
-            march_tile<ST, NT, P, 128, D, X>(d, c, i_begin, i_end, lds);
+            march_tile<ST, NT, P, 128, true, D, X>(d, c, i_begin, i_end, lds);
         }
     }
 }
@@ -412,6 +414,9 @@ template <typename ST, int P>
 int occupancy_kind(int32_t kind, int64_t lds_bytes) {
     switch (kind) {
         case kFixedNz: return occupancy_of<ST, P, kFixedNz>(lds_bytes);
+        case kEven0: return occupancy_of<ST, P, kEven0>(lds_bytes);
+        case kEven1: return occupancy_of<ST, P, kEven1>(lds_bytes);
+        case kEven2: return occupancy_of<ST, P, kEven2>(lds_bytes);
         case kClass0: return occupancy_of<ST, P, kClass0>(lds_bytes);
         case kClass1: return occupancy_of<ST, P, kClass1>(lds_bytes);
         case kClass2: return occupancy_of<ST, P, kClass2>(lds_bytes);
@@ -446,6 +451,9 @@ template <typename ST, int P>
 hipError_t dispatch_kind(int32_t kind, const BatchedLaunch& bl, const pw_domain_args* args, hipStream_t stream) {
     switch (kind) {
         case kFixedNz: return launch_batched<ST, P, kFixedNz>(bl, args, stream);
+        case kEven0: return launch_batched<ST, P, kEven0>(bl, args, stream);
+        case kEven1: return launch_batched<ST, P, kEven1>(bl, args, stream);
+        case kEven2: return launch_batched<ST, P, kEven2>(bl, args, stream);
         case kClass0: return launch_batched<ST, P, kClass0>(bl, args, stream);
         case kClass1: return launch_batched<ST, P, kClass1>(bl, args, stream);
         case kClass2: return launch_batched<ST, P, kClass2>(bl, args, stream);
@@ -529,7 +537,7 @@ int32_t batched_launch_shape(int32_t storage, const pw_shape* shapes, int32_t n,
     const int32_t seg_max = t.seg ? t.seg : (elem_bytes(storage) >= 4 ? 16 : 64);
     int32_t nzmax = 0;
     int64_t tiles = 0;
-    bool vec = true, fixed_nz = true;
+    bool vec = true, fixed_nz = true, even = true;
     for (int32_t d = 0; d < n; ++d) {
         pw_shape s;
         (void)normalize_shape(shapes[d], &s);   // checked above
@@ -539,14 +547,15 @@ int32_t batched_launch_shape(int32_t storage, const pw_shape* shapes, int32_t n,
         nzmax = std::max(nzmax, s.nz);
         vec = vec && vector_shape(storage, s);
         fixed_nz = fixed_nz && compiled_height(s.nz);
+        even = even && s.nz % 2 == 0;
     }
     Launch r{};
     r.variant = PW_VARIANT_MARCH;
     r.chunk = chunk;
     r.seg = seg_max;
     r.block = 256;
-    const int32_t k = vec && fixed_nz ? kFixedNz : kClass0 + height_class(nzmax);
-    r.lds_bytes = march_lds_bytes(storage, chunk, k == kFixedNz ? nzmax : -kHeightClass[k - kClass0]);
+    const int32_t k = vec && fixed_nz ? kFixedNz : (even ? kEven0 : kClass0) + height_class(nzmax);
+    r.lds_bytes = march_lds_bytes(storage, chunk, k == kFixedNz ? nzmax : -kHeightClass[kind_class(k)]);
     if (r.lds_bytes > kMaxDynamicLds) return PW_ERR_UNSUPPORTED;
     r.tiles = tiles;
     int dev = 0, cus = 0;

@@ -630,12 +630,13 @@ struct DirectPair {
 // whole vectors, at element alignment (the hardware takes 8- and 16-byte
 // accesses at any dword for the same number of cache lines, 16-bit pairs at
 // any halfword); the last vector of a window that is no multiple of VW starts
-// early and overlaps the one before it.  A pair of points may straddle two
-// columns (odd heights), so both points select their bottom and top results,
-// and a last chunk of an odd number of points ends with a pair that starts one
-// point early (same values stored twice).
+// early and overlaps the one before it.  EVEN (an even height): pairs of
+// points are pairs of levels, aligned in LDS.  Otherwise a pair may straddle
+// two columns, so both points select their bottom and top results, LDS reads
+// are only aligned to an element, and a last chunk of an odd number of points
+// ends with a pair that starts one point early (same values stored twice).
 constexpr int march_wpad(int p, int nz) { return round_up4(p + 2 * (nz > 0 ? nz : -nz)); }
-template <typename ST, int NT, int P, int NZ, int DIST = 2, bool FORCE_EXACT = false>
+template <typename ST, int NT, int P, int NZ, bool EVEN = true, int DIST = 2, bool FORCE_EXACT = false>
 struct MarchTile {
     using CT = typename compute_of<ST>::type;
     // Elements per load: as many as fill 16 bytes of LDS in the compute type,
@@ -647,7 +648,8 @@ struct MarchTile {
     static constexpr int PPT = P / NT;                                     // points per thread
     static constexpr bool RT = NZ < 0;                                     // run-time height, element alignment
     static constexpr bool PAIR = P % (2 * NT) == 0;
-    static_assert(RT || NZ % 2 == 0, "pairs of levels need an even compiled height");
+    static_assert(RT || (NZ % 2 == 0 && EVEN), "pairs of levels need an even compiled height");
+    static constexpr bool ANY = RT && !EVEN;                               // pairs may straddle columns
     // Branch-free data movement (see the constructor) where storage is
     // narrower than the compute type: those kernels are bound by instruction
     // issue, and exact load counting lets two planes stay in flight.  FP32
@@ -661,7 +663,9 @@ struct MarchTile {
     static_assert(VW * sizeof(ST) == 16 || VW * sizeof(ST) == 8, "8- or 16-byte loads");
     using Raw = typename std::conditional<VW * sizeof(ST) == 16, uint4, uint2>::type;
     static constexpr int RAW_ALIGN = RT ? int(sizeof(ST)) : int(sizeof(Raw));
-    static constexpr int PAIR_ALIGN = RT ? 1 : 2;   // elements a pair's window index is a multiple of
+    static constexpr int PAIR_ALIGN = ANY ? 1 : 2;   // elements a pair's window index is a multiple of
+    // bytes an LDS write of a vector is aligned to
+    static constexpr int PUT_ALIGN = !RT ? 16 : (ANY ? int(sizeof(CT)) : int(2 * sizeof(CT)));
     using V2 = typename lds_pair<CT, PAIR_ALIGN>::type;
     static_assert(P % NT == 0, "P must be a multiple of the block size");
 
@@ -725,7 +729,7 @@ struct MarchTile {
         pend = min(p0 + P, (d.ny + 1) * n);             // one past the last interior point
         // a pair needs two points: a last chunk of one starts a point early
         // (never the only chunk, which has at least nz >= 2)
-        if (RT && PAIR && pend - p0 == 1) --p0;
+        if (ANY && PAIR && pend - p0 == 1) --p0;
         wb = p0 - n;                                    // window start: one column of y halo
         wlen = min(P + 2 * n, (d.ny + 2) * n - wb);
         const int nvec = (wlen + VW - 1) / VW;   // vectors per field (wlen >= 5 >= VW; NZ > 0: a multiple of VW)
@@ -779,8 +783,8 @@ struct MarchTile {
             for (int q = 0; q < PPT; ++q) {
                 const CT h[6] = {hx[0], hy[0], hy[1], hx[1], hx[2], hy[2]};
                 // even heights: the first level of a pair is odd, the second even
-                const bool bottom = (RT || q % 2 == 0) && kk[q] == 1;
-                const bool top = (RT || q % 2 == 1) && kk[q] == nz();
+                const bool bottom = (ANY || q % 2 == 0) && kk[q] == 1;
+                const bool top = (ANY || q % 2 == 1) && kk[q] == nz();
 #pragma unroll
                 for (int e = 0; e < 6; ++e) ph[q][e] = (bottom || (top && e >= 4)) ? CT(0) : h[e];
                 if (bottom) {
@@ -838,7 +842,7 @@ struct MarchTile {
                     for (int n = 0; n < VW; ++n) out[n] = to_compute(cv.e[n]);
                 }
                 static_assert(VW * sizeof(CT) == 16, "one 16-byte LDS write per vector");
-                using V4 = typename vec_at<uint32_t, 4, RT ? (int)sizeof(CT) : 16>::type;
+                using V4 = typename vec_at<uint32_t, 4, PUT_ALIGN>::type;
                 V4 x;
                 __builtin_memcpy(&x, out, 16);
                 *reinterpret_cast<V4*>(slot + loff[r]) = x;
@@ -937,10 +941,10 @@ struct MarchTile {
                 if (q % 2 == 0) gather_blocks<0>(blk[q / 2], q / 2, sm, sc, sp);
                 if (q % 2 == 0) {
                     CachedPairAcc<CT, V2, 0> A{blk[q / 2]};
-                    pw_point<AR, false, !ZEND, RT && !ZEND>(A, kk[q], nz(), c, res[q][0], res[q][1], res[q][2], xs[q]);
+                    pw_point<AR, false, !ZEND, ANY && !ZEND>(A, kk[q], nz(), c, res[q][0], res[q][1], res[q][2], xs[q]);
                 } else {
                     CachedPairAcc<CT, V2, 1> A{blk[q / 2]};
-                    pw_point<AR, false, RT && !ZEND, !ZEND>(A, kk[q], nz(), c, res[q][0], res[q][1], res[q][2], xs[q]);
+                    pw_point<AR, false, ANY && !ZEND, !ZEND>(A, kk[q], nz(), c, res[q][0], res[q][1], res[q][2], xs[q]);
                     keep_blocks<0>(blk[q / 2], q / 2);
                 }
             } else if constexpr (PAIR) {
@@ -949,10 +953,10 @@ struct MarchTile {
                 // possible)
                 if (q % 2 == 0) {
                     PairAcc<CT, WPAD, PAIR_ALIGN, 0> A{row[q / 2], sm, sc, sp};
-                    pw_point<AR, false, true, RT>(A, kk[q], nz(), c, res[q][0], res[q][1], res[q][2]);
+                    pw_point<AR, false, true, ANY>(A, kk[q], nz(), c, res[q][0], res[q][1], res[q][2]);
                 } else {
                     PairAcc<CT, WPAD, PAIR_ALIGN, 1> A{row[q / 2], sm, sc, sp};
-                    pw_point<AR, false, RT, true>(A, kk[q], nz(), c, res[q][0], res[q][1], res[q][2]);
+                    pw_point<AR, false, ANY, true>(A, kk[q], nz(), c, res[q][0], res[q][1], res[q][2]);
                 }
             } else {
                 LdsAcc<CT, NZ, WPAD> A{lds + sm * SLOT + l, lds + sc * SLOT + l, lds + sp * SLOT + l, nz_rt};
@@ -966,7 +970,7 @@ struct MarchTile {
             for (int q = 0; q < PPT; q += 2) {
                 if (!CLAMP && !live[q]) continue;   // NZ > 0: a pair never straddles the chunk end (P, nz even)
 #pragma unroll
-                for (int f = 0; f < 3; ++f) store_pair<ST, PAIR_ALIGN>(outs[f] + (uint32_t)li[q], res[q][f], res[q + 1][f]);
+                for (int f = 0; f < 3; ++f) store_pair<ST, RT ? 1 : 2>(outs[f] + (uint32_t)li[q], res[q][f], res[q + 1][f]);
             }
         } else {
 #pragma unroll
@@ -1044,10 +1048,10 @@ struct MarchTile {
     }
 };
 
-template <typename ST, int NT, int P, int NZ, int DIST = 2, bool FORCE_EXACT = false>
+template <typename ST, int NT, int P, int NZ, bool EVEN = true, int DIST = 2, bool FORCE_EXACT = false>
 __device__ __forceinline__ void march_tile(const DomainArgs& d, int c, int i_begin, int i_end,
                                            typename compute_of<ST>::type* lds) {
-    MarchTile<ST, NT, P, NZ, DIST, FORCE_EXACT> t(d, c, lds);
+    MarchTile<ST, NT, P, NZ, EVEN, DIST, FORCE_EXACT> t(d, c, lds);
     t.run(i_begin, i_end);
 }
 
@@ -1083,7 +1087,7 @@ __global__ __launch_bounds__(512) void pw_direct_kernel(DomainArgs d, MarchGeom 
 }
 
 // March variant: one workgroup per (chunk, segment) tile.
-template <typename ST, int NT, int P, int NZ>
+template <typename ST, int NT, int P, int NZ, bool EVEN>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, march_max_waves<ST>())))
 void pw_march_kernel(DomainArgs d, MarchGeom g) {
     using CT = typename compute_of<ST>::type;
@@ -1091,7 +1095,7 @@ void pw_march_kernel(DomainArgs d, MarchGeom g) {
     CT* lds = reinterpret_cast<CT*>(smem_raw);
     int c, i_begin, i_end;
     if (!single_tile(g, d.nx, c, i_begin, i_end)) return;
-    march_tile<ST, NT, P, NZ>(d, c, i_begin, i_end, lds);
+    march_tile<ST, NT, P, NZ, EVEN>(d, c, i_begin, i_end, lds);
 }
 
 }  // namespace pw
