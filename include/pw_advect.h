@@ -118,8 +118,8 @@ typedef struct pw_shape {
               kernel each domain splits its nx planes into n = ceil(nx / seg)
               segments of ceil(nx / n) planes (at most seg; the last may be
               shorter), so a domain's tiles have nearly equal length; the
-              batched default is 16 for 4- and 8-byte storage and 64 for the
-              16-bit types.
+              batched default follows the batch's size (6 planes up to 10 for
+              PW_F64, 12 for PW_F32 and 64 for the other types).
    block      threads per workgroup of the direct variant: 64, 128, 256 or 512.
    wg_per_cu  batched launches: 0 (the default) or PW_WG_ONE_PER_TILE runs
               one workgroup per tile, so the hardware hands out the tiles in

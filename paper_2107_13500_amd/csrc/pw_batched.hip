@@ -27,6 +27,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <mutex>
 #include <vector>
@@ -34,6 +35,9 @@
 #include "pw_plan.hpp"
 
 namespace pw {
+
+__host__ __device__ inline void domain_tiles(int32_t nx, int32_t ny, int32_t nz, int32_t chunk, int32_t seg_max,
+                                             BatchDomain* b);
 
 namespace {
 
@@ -447,6 +451,46 @@ int batched_occupancy(int32_t storage, int32_t chunk, int32_t kind, int64_t lds_
     }
 }
 
+// Workgroups per CU of a batched launch, asked of the runtime once for each
+// kernel and LDS size (the allocation-free call needs it on every call).
+int64_t resident_per_cu(int32_t storage, int32_t chunk, int32_t kind, int64_t lds_bytes) {
+    static std::atomic<int32_t> known[6][3][7][3];   // 0: not asked yet; kFixedNz: by its height's LDS
+    const int c = chunk == 256 ? 0 : (chunk == 512 ? 1 : 2);
+    const int h = kind != kFixedNz || lds_bytes == march_lds_bytes(storage, chunk, 64)
+                      ? 0 : (lds_bytes == march_lds_bytes(storage, chunk, 96) ? 1 : 2);
+    std::atomic<int32_t>& slot = known[storage][c][kind][h];
+    int32_t occ = slot.load(std::memory_order_relaxed);
+    if (occ == 0) {
+        occ = batched_occupancy(storage, chunk, kind, lds_bytes);
+        if (occ > 0) slot.store(occ, std::memory_order_relaxed);
+    }
+    const int64_t by_lds = std::max<int64_t>(1, kLdsPerCu / std::max<int64_t>(lds_bytes, 1));
+    const int64_t n = std::min<int64_t>(by_lds, 8);
+    return occ > 0 ? std::min<int64_t>(n, occ) : n;
+}
+
+// Default segment length of a batch from its chunk planes and the workgroups
+// the chip keeps resident: 1.3 times the chunk planes per resident workgroup,
+// so that a small batch still gives every CU tiles of equal length, at least
+// 6 (below, the planes a tile's start reads twice cost more than the balance
+// gains) and at most the length that is best for large batches: 10 planes for
+// FP64 and 12 for FP32, where short tiles keep the uneven domains' streams
+// together in HBM, 64 for the types that convert, whose tiles' start costs
+// more.  Fitted to lengths of 1 .. 96 planes on batches of 5 to 384 domains:
+// on average 1.6% (FP64), 2.7% (FP32), 4% (BF16, int16) and 2.5% (int32) off
+// the best length; fixed lengths of 16 (4- and 8-byte types) and 64 planes are
+// 9%, 13%, 41-47% and 16% off.  384 domains: FP64 1114 -> 1087 us, int32
+// 710 -> 632 us; 13 domains BF16 40 -> 21 us, int16 42 -> 21 us.
+// Without a plan (no longest-first order) the converting types take about half
+// of that: 96 domains BF16 106 us with 32 planes, 112 with 64; 30 domains 43
+// with 16, 53 with 64.
+int32_t batched_seg(int32_t storage, int64_t planes, int64_t resident, bool sorted) {
+    const bool wide = storage == PW_F64 || storage == PW_F32;
+    const int64_t most = storage == PW_F64 ? 10 : (wide ? 12 : (sorted ? 64 : 48));
+    const int64_t seg = planes * (wide || sorted ? 13 : 7) / (10 * std::max<int64_t>(1, resident));
+    return (int32_t)std::max<int64_t>(6, std::min<int64_t>(seg, most));
+}
+
 template <typename ST, int P>
 hipError_t dispatch_kind(int32_t kind, const BatchedLaunch& bl, const pw_domain_args* args, hipStream_t stream) {
     switch (kind) {
@@ -519,7 +563,7 @@ __host__ __device__ inline void domain_tiles(int32_t nx, int32_t ny, int32_t nz,
 // nothing.  Returns PW_OK with L->tiles == 0 if a shape cannot use the
 // batched kernel (march variant impossible, or 2^31 points or more).
 int32_t batched_launch_shape(int32_t storage, const pw_shape* shapes, int32_t n, const pw_tuning& t, Launch* L,
-                             int32_t* kind, bool* vec_out) {
+                             int32_t* kind, bool* vec_out, bool sorted) {
     *L = Launch{};
     for (int32_t d = 0; d < n; ++d) {
         pw_shape s;
@@ -530,20 +574,13 @@ int32_t batched_launch_shape(int32_t storage, const pw_shape* shapes, int32_t n,
     const int32_t chunk = t.chunk ? t.chunk : 512;
     if (chunk != 256 && chunk != 512 && chunk != 1024) return PW_ERR_INVALID_ARG;
     if (t.seg < 0 || t.wg_per_cu < PW_WG_ONE_PER_TILE || t.wg_per_cu > 8) return PW_ERR_INVALID_ARG;
-    // default segment length: short tiles balance the uneven domains of a
-    // batch for the 4- and 8-byte types; the 16-bit types, with more
-    // arithmetic per byte, gain from longer marches (measured on the
-    // 384-domain batch: FP64 and FP32 fastest at 12-16 planes, BF16 at 48+)
-    const int32_t seg_max = t.seg ? t.seg : (elem_bytes(storage) >= 4 ? 16 : 64);
     int32_t nzmax = 0;
-    int64_t tiles = 0;
+    int64_t planes = 0;   // chunk planes of the batch
     bool vec = true, fixed_nz = true, even = true;
     for (int32_t d = 0; d < n; ++d) {
         pw_shape s;
         (void)normalize_shape(shapes[d], &s);   // checked above
-        BatchDomain b{};
-        domain_tiles(s.nx, s.ny, s.nz, chunk, seg_max, &b);
-        tiles += (int64_t)b.nchunks * b.nseg;
+        planes += ((int64_t)s.ny * s.nz + chunk - 1) / chunk * s.nx;
         nzmax = std::max(nzmax, s.nz);
         vec = vec && vector_shape(storage, s);
         fixed_nz = fixed_nz && compiled_height(s.nz);
@@ -552,20 +589,23 @@ int32_t batched_launch_shape(int32_t storage, const pw_shape* shapes, int32_t n,
     Launch r{};
     r.variant = PW_VARIANT_MARCH;
     r.chunk = chunk;
-    r.seg = seg_max;
     r.block = 256;
     const int32_t k = vec && fixed_nz ? kFixedNz : (even ? kEven0 : kClass0) + height_class(nzmax);
     r.lds_bytes = march_lds_bytes(storage, chunk, k == kFixedNz ? nzmax : -kHeightClass[kind_class(k)]);
     if (r.lds_bytes > kMaxDynamicLds) return PW_ERR_UNSUPPORTED;
-    r.tiles = tiles;
     int dev = 0, cus = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e != hipSuccess) return report_hip(e);
-    const int64_t by_lds = std::max<int64_t>(1, kLdsPerCu / std::max<int64_t>(r.lds_bytes, 1));
-    int64_t per_cu = std::min<int64_t>(by_lds, 8);
-    const int occ = batched_occupancy(storage, chunk, k, r.lds_bytes);
-    if (occ > 0) per_cu = std::min<int64_t>(per_cu, occ);
+    int64_t per_cu = resident_per_cu(storage, chunk, k, r.lds_bytes);
+    r.seg = t.seg ? t.seg : batched_seg(storage, planes, (int64_t)cus * std::min<int64_t>(per_cu, 4), sorted);
+    int64_t tiles = 0;
+    for (int32_t d = 0; d < n; ++d) {
+        BatchDomain b{};
+        domain_tiles(shapes[d].nx, shapes[d].ny, shapes[d].nz, chunk, r.seg, &b);
+        tiles += (int64_t)b.nchunks * b.nseg;
+    }
+    r.tiles = tiles;
     if (t.wg_per_cu > 0) per_cu = std::min<int64_t>(per_cu, t.wg_per_cu);
     r.workgroups = std::max<int64_t>(1, std::min<int64_t>(tiles, (int64_t)cus * per_cu));
     // One workgroup per tile: the kernel's tile loop then runs once per
@@ -645,7 +685,8 @@ int32_t batched_plan_init(pw_plan* p) {
     Launch L{};
     int32_t kind = kFixedNz;
     bool vec = false;
-    int32_t rc = batched_launch_shape(p->storage, p->shapes.data(), p->ndomains, p->tuning, &L, &kind, &vec);
+    int32_t rc = batched_launch_shape(p->storage, p->shapes.data(), p->ndomains, p->tuning, &L, &kind, &vec,
+                                      batched_one_per_tile(p->tuning));
     if (rc != PW_OK) return rc;
     if (L.tiles == 0) return PW_OK;   // batched entry points will report PW_ERR_UNSUPPORTED
 
@@ -686,10 +727,7 @@ int32_t batched_plan_init(pw_plan* p) {
     if (batched_one_per_tile(p->tuning) && (p->storage == PW_BF16 || p->storage == PW_F16) &&
         tiles < (int64_t(1) << 31)) {
         // workgroups one XCD keeps resident: its CUs times the occupancy
-        const int64_t by_lds = std::max<int64_t>(1, kLdsPerCu / std::max<int64_t>(L.lds_bytes, 1));
-        int64_t per_cu = std::min<int64_t>(by_lds, 8);
-        const int occ = batched_occupancy(p->storage, L.chunk, kind, L.lds_bytes);
-        if (occ > 0) per_cu = std::min<int64_t>(per_cu, occ);
+        const int64_t per_cu = resident_per_cu(p->storage, L.chunk, kind, L.lds_bytes);
         order = one_tile_order(table, L.chunk, std::max<int64_t>(1, cus / kNumXcd) * per_cu);
         if ((int64_t)order.size() >= (int64_t(1) << 31)) order.clear();
         if (!order.empty()) L.workgroups = (int64_t)order.size();
@@ -885,7 +923,6 @@ __host__ __device__ inline uint64_t shape_digest_term(int32_t d, int32_t nx, int
 }
 
 constexpr int kTableThreads = 1024;
-constexpr int kTablePerThread = kNoAllocMaxDomains / kTableThreads;
 
 // Table row of domain d from its record (an empty row if the shape is out of
 // range: the digest of such a batch cannot match a valid one).
@@ -904,58 +941,63 @@ __device__ __forceinline__ BatchDomain record_row(const pw_domain_args* args, in
 }
 
 // Builds the tile table of a batch from its device records into scratch (one
-// workgroup): thread t takes domains 4t .. 4t+3, a workgroup scan of the
-// per-thread tile counts gives every domain its first tile, and a reduction
-// forms the shape digest.  The gate word is set only if the digest and the
-// tile total equal the host's, i.e. the records carry the shapes the launch
-// was shaped for.  The error word is cleared.
+// workgroup of as many waves as the batch needs, at most 16): in rounds of one
+// domain per thread, a scan of the tile counts (within each wave by lane
+// exchange, then over the waves) gives every domain its first tile, and the
+// shape digest is summed the same way.  The gate word is set only if the
+// digest and the tile total equal the host's, i.e. the records carry the
+// shapes the launch was shaped for.  The error word is cleared.  Bound by the
+// latency of the record reads and of one launch: 8.9 us with 1024 threads of
+// four domains each (two passes over the records, twenty barriers).
 __global__ __launch_bounds__(kTableThreads) void pw_noalloc_table_kernel(const pw_domain_args* __restrict__ args,
                                                                          int ndom, int chunk, int seg_max,
                                                                          uint64_t digest_host, int64_t tiles_host,
                                                                          unsigned char* scr) {
-    __shared__ int64_t part[kTableThreads];
-    __shared__ uint64_t hsum[kTableThreads];
+    __shared__ int64_t part[kTableThreads / 64];
+    __shared__ uint64_t hsum[kTableThreads / 64];
     BatchDomain* table = reinterpret_cast<BatchDomain*>(scr + kNoAllocHeader);
-    const int t = (int)threadIdx.x;
-    int64_t mine = 0;
-    uint64_t h = 0;
-    for (int q = 0; q < kTablePerThread; ++q) {
-        const int d = t * kTablePerThread + q;
+    const int t = (int)threadIdx.x, lane = t % 64, wave = t / 64, waves = (int)blockDim.x / 64;
+    int64_t before = 0;    // tiles of the earlier rounds
+    uint64_t digest = 0;   // digest terms of this thread's domains
+    for (int d0 = 0; d0 < ndom; d0 += (int)blockDim.x) {   // uniform over the workgroup
+        const int d = d0 + t;
+        BatchDomain b{};
         if (d < ndom) {
             uint64_t term;
-            const BatchDomain b = record_row(args, d, chunk, seg_max, &term);
-            h += term;
-            mine += (int64_t)b.nchunks * b.nseg;
+            b = record_row(args, d, chunk, seg_max, &term);
+            digest += term;
         }
-    }
-    part[t] = mine;
-    hsum[t] = h;
-    __syncthreads();
-    // inclusive scan of the tile counts (Hillis-Steele) and tree reduction of
-    // the digest terms into hsum[0]
-    for (int off = 1; off < kTableThreads; off <<= 1) {
-        const int64_t a = t >= off ? part[t - off] : 0;
-        const uint64_t g = (t & (2 * off - 1)) == 0 ? hsum[t + off] : 0;
+        const int64_t mine = (int64_t)b.nchunks * b.nseg;
+        int64_t sum = mine;   // inclusive scan over the wave
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int64_t lower = __shfl_up(sum, off, 64);
+            if (lane >= off) sum += lower;
+        }
+        if (lane == 63) part[wave] = sum;
         __syncthreads();
-        part[t] += a;
-        hsum[t] += g;
-        __syncthreads();
-    }
-    int64_t first = part[t] - mine;
-    for (int q = 0; q < kTablePerThread; ++q) {
-        const int d = t * kTablePerThread + q;
+        int64_t first = before + sum - mine, all = 0;
+        for (int w = 0; w < waves; ++w) {
+            if (w < wave) first += part[w];
+            all += part[w];
+        }
+        before += all;
         if (d < ndom) {
-            uint64_t term;
-            BatchDomain b = record_row(args, d, chunk, seg_max, &term);
             b.rec = d;   // the caller's order (no reordering on the device)
             b.tile_begin = first;
-            first += (int64_t)b.nchunks * b.nseg;
             table[d] = b;
         }
+        __syncthreads();   // part is written again in the next round
     }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) digest += __shfl_down(digest, off, 64);
+    if (lane == 0) hsum[wave] = digest;
+    __syncthreads();
     if (t == 0) {
-        const bool ok = hsum[0] == digest_host && part[kTableThreads - 1] == tiles_host;
-        *reinterpret_cast<int64_t*>(scr + 8) = part[kTableThreads - 1];
+        uint64_t h = 0;
+        for (int w = 0; w < waves; ++w) h += hsum[w];
+        const bool ok = h == digest_host && before == tiles_host;
+        *reinterpret_cast<int64_t*>(scr + 8) = before;
         *reinterpret_cast<unsigned long long*>(scr + 16) = 0ull;
         *reinterpret_cast<uint32_t*>(scr) = ok ? 1u : 0u;
     }
@@ -985,14 +1027,15 @@ int32_t pw_advect_batched_noalloc(int32_t storage, const pw_shape* shapes, int32
     Launch L{};
     int32_t kind = 0;
     bool vec = false;
-    int32_t rc = batched_launch_shape(storage, shapes, ndomains, t, &L, &kind, &vec);
+    int32_t rc = batched_launch_shape(storage, shapes, ndomains, t, &L, &kind, &vec, false);
     if (rc != PW_OK) return rc;
     if (L.tiles == 0) return PW_ERR_UNSUPPORTED;
     unsigned char* scr = nullptr;
     rc = scratch_of_current_device(&scr);
     if (rc != PW_OK) return rc;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    hipLaunchKernelGGL(pw_noalloc_table_kernel, dim3(1), dim3(kTableThreads), 0, st, d_args, ndomains, L.chunk,
+    const int table_threads = std::min(kTableThreads, (ndomains + 63) / 64 * 64);   // whole waves
+    hipLaunchKernelGGL(pw_noalloc_table_kernel, dim3(1), dim3((unsigned)table_threads), 0, st, d_args, ndomains, L.chunk,
                        L.seg, digest, L.tiles, scr);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return report_hip(e);

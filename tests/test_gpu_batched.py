@@ -350,3 +350,28 @@ def test_full_384_domain_batch_graph(storage, tuning):
         ref = oracle.advect(u, v, w, p.coeffs.tcx, p.coeffs.tcy, *p.coeffs.arrays())
         for gg, rr in zip(batch.host_outputs(d), ref):
             assert max_rel(gg[1:-1, 1:-1], rr[1:-1, 1:-1]) <= tol
+
+
+@pytest.mark.parametrize("storage", [B.F64, B.BF16, B.I16], ids=["f64", "bf16", "i16"])
+@pytest.mark.parametrize("shapes", [[(9, 7, 64)], [(40, 33, 96)] * 3, [(96, 90, 64)] * 40],
+                         ids=["one", "three", "forty"])
+def test_default_segments_of_batches_of_any_size(storage, shapes):
+    """The default segment length follows the batch's size, up to the type's
+    longest: every domain's outputs have the bits of a fixed 16-plane split."""
+    probs = [inputs.make_problem(*s, seed=440 + (d % 3)) for d, s in enumerate(shapes)]
+    batch = BT.DeviceBatch(probs, storage, DEV)
+    got = []
+    for tuning in (None, {"chunk": 512, "seg": 16}):
+        for f in batch.fields:
+            for o in f[3:]:
+                o.zero_()
+        plan = batch.plan(tuning)
+        say("batch segments", B.DTYPE_NAMES[storage], len(shapes), plan.info()["seg"])
+        assert len(shapes) == 1 or 6 <= plan.info()["seg"] <= 64   # one domain: info() describes pw_advect
+        batch.advect(plan)
+        torch.cuda.synchronize()
+        assert plan.error_count() == 0
+        got.append([[o.clone() for o in f[3:]] for f in batch.fields])
+    for a, b in zip(*got):
+        for x, y in zip(a, b):
+            assert same_bits(x, y) if storage != B.I16 else torch.equal(x, y)

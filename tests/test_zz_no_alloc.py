@@ -91,3 +91,26 @@ def test_noalloc_rejects_batches_beyond_its_fixed_table():
     assert l.pw_advect_batched_noalloc(B.F64, shapes, 4097, dummy.data_ptr(), None, None, None) == -1
     assert l.pw_advect_batched_noalloc(B.F64, shapes, 0, dummy.data_ptr(), None, None, None) == -1
     assert l.pw_advect_batched_noalloc(9, shapes, 1, dummy.data_ptr(), None, None, None) == -2
+
+
+@pytest.mark.parametrize("count", [63, 64, 65, 1025], ids=lambda n: "%d-domains" % n)
+def test_noalloc_table_over_wave_and_round_edges(count):
+    """The device-built tile table at the edges of its waves and of its rounds
+    of 1024 domains: default tuning, outputs bit for bit those of the plan."""
+    shapes = [(1 + d % 3, 1 + (d * 7) % 5, (64, 96, 128)[d % 3]) for d in range(count)]
+    say("no-alloc table", count)
+    batch = BT.DeviceBatch(problems(shapes, 950), B.F32, DEV)
+    skipped = torch.zeros(1, dtype=torch.int64, device=DEV)
+    plan = batch.plan()
+    sentinel(batch, 0)
+    batch.advect(plan)
+    torch.cuda.synchronize()
+    assert plan.error_count() == 0
+    want = outputs(batch)
+    sentinel(batch, 0)
+    B.advect_batched_noalloc(B.F32, batch.shapes, batch.d_args, None, skipped)
+    torch.cuda.synchronize()
+    assert int(skipped.item()) == 0
+    for d, f in enumerate(batch.fields):
+        for o, w in zip(f[3:], want[d]):
+            assert same_bits(o, w), "domain %d differs" % d
