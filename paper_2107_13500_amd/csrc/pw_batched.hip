@@ -142,10 +142,11 @@ __global__ __launch_bounds__(NT) void pw_batched_kernel(const BatchDomain* __res
                                                         int64_t ntiles, const pw_domain_args* __restrict__ args,
                                                         unsigned long long* errors,
                                                         int vec_shapes, int one_per_tile, const int32_t* __restrict__ order,
-                                                        const uint32_t* gate) {
+                                                        const uint32_t* gate, unsigned long long* bump) {
     using CT = typename compute_of<ST>::type;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     CT* lds = reinterpret_cast<CT*>(smem_raw);
+    if (bump != nullptr && blockIdx.x == 0 && threadIdx.x == 0) *bump += 1ull;   // a timestep's call counter
     if (gate != nullptr && *gate == 0u) {   // uniform over the grid
         if (blockIdx.x == 0 && threadIdx.x == 0) atomicAdd(errors, (unsigned long long)ndom);
         return;
@@ -310,14 +311,23 @@ __device__ __forceinline__ uint32_t lowbias32(uint32_t x) {
 // the (j, k) points of a plane times a segment of x planes), so every
 // workgroup of the grid has work whatever the spread of domain sizes; each
 // thread reads the points of kPerturbPlanes planes before it writes them.
+//
+// HALO (the recorded timestep): also the periodic halo of u, v, w, written
+// from the values in hand -- a boundary point's copies go out with it, only
+// w's boundary columns are read besides -- with the result of pw_halo_kernel
+// after this kernel.  On 384 domains the halo pass costs 84 us (FP32) by
+// itself, which reads again what this kernel has just written.
 constexpr int kPerturbPlanes = 4;
 
-template <typename ST>
+template <typename ST, bool HALO>
 __global__ __launch_bounds__(256) void pw_perturb_kernel(const BatchDomain* __restrict__ table, int ndom, int chunk,
                                                          const pw_domain_args* __restrict__ args, uint64_t seed,
                                                          const unsigned long long* __restrict__ call, double amp) {
     using CT = typename compute_of<ST>::type;
-    const int64_t t = blockIdx.x;
+    // HALO: from the last tile to the first, so that the advection after it,
+    // which begins with the first tiles, finds the fields written last in the
+    // last-level cache (and so does the next step's perturbation)
+    const int64_t t = HALO ? (int64_t)(gridDim.x - 1 - blockIdx.x) : (int64_t)blockIdx.x;
     const BatchDomain b = table[find_domain(table, ndom, t)];
     const int dom = b.rec;   // the caller's domain index keys the hash
     const pw_domain_args& a = args[dom];
@@ -332,7 +342,7 @@ __global__ __launch_bounds__(256) void pw_perturb_kernel(const BatchDomain* __re
     const uint64_t key64 = splitmix64(seed ^ splitmix64((uint64_t)(*call) * 0x100000001b3ull + (uint64_t)dom));
     const uint32_t key = (uint32_t)key64 ^ (uint32_t)(key64 >> 32);
     using U = storage_bits<ST>;
-    global_ptr<U> f[2] = {as_global((U*)a.u), as_global((U*)a.v)};
+    global_ptr<U> f[3] = {as_global((U*)a.u), as_global((U*)a.v), as_global((U*)a.w)};
     const CT sc[2] = {static_cast<CT>(scaled_type<ST>::value ? scale_or_one(a.scales.in_scale[0]) : 1.0f),
                       static_cast<CT>(scaled_type<ST>::value ? scale_or_one(a.scales.in_scale[1]) : 1.0f)};
     uint32_t p = 0;
@@ -347,6 +357,36 @@ __global__ __launch_bounds__(256) void pw_perturb_kernel(const BatchDomain* __re
         const uint32_t k = p % nz;
         const uint32_t j = p / nz + 1;
         const int64_t col = k + (int64_t)j * b.sy;
+        // halo columns that copy this one (both may for ny = 1)
+        const bool to_lo = HALO && (int)j == b.ny, to_hi = HALO && j == 1;
+        auto across = [&](global_ptr<U> g, int64_t plane, U x) {   // the row's own halo columns in a plane
+            if (to_lo) g[k + plane] = x;
+            if (to_hi) g[k + (int64_t)(b.ny + 1) * b.sy + plane] = x;
+        };
+        auto spread = [&](global_ptr<U> g, int i, U x) {
+            across(g, (int64_t)i * b.sx, x);
+            if (i == b.nx) {   // plane 0 copies plane nx
+                g[col] = x;
+                across(g, 0, x);
+            }
+            if (i == 1) {      // plane nx + 1 copies plane 1
+                const int64_t plane = (int64_t)(b.nx + 1) * b.sx;
+                g[col + plane] = x;
+                across(g, plane, x);
+            }
+        };
+        auto put = [&](int i, int q, U x) {
+            f[q][col + (int64_t)i * b.sx] = x;
+            if (HALO) spread(f[q], i, x);
+        };
+        if (HALO) {
+            if (to_lo || to_hi) {
+                for (int i = i0; i <= i1; ++i) spread(f[2], i, f[2][col + (int64_t)i * b.sx]);
+            } else {
+                if (i0 == 1) spread(f[2], 1, f[2][col + b.sx]);
+                if (i1 == b.nx && (b.nx > 1 || i0 != 1)) spread(f[2], b.nx, f[2][col + (int64_t)b.nx * b.sx]);
+            }
+        }
         // full groups of kPerturbPlanes planes without conditions (so the
         // compiler keeps all their loads in flight), then the rest one by one
         int i = i0;
@@ -360,13 +400,13 @@ __global__ __launch_bounds__(256) void pw_perturb_kernel(const BatchDomain* __re
             for (int u = 0; u < kPerturbPlanes; ++u)
 #pragma unroll
                 for (int q = 0; q < 2; ++q)
-                    f[q][col + (int64_t)(i + u) * b.sx] = to_bits(from_compute<ST>(perturbed(x[u][q], i + u, q)));
+                    put(i + u, q, to_bits(from_compute<ST>(perturbed(x[u][q], i + u, q))));
         }
         for (; i <= i1; ++i) {
 #pragma unroll
             for (int q = 0; q < 2; ++q) {
                 const CT x = to_compute(from_bits<ST>(f[q][col + (int64_t)i * b.sx]));
-                f[q][col + (int64_t)i * b.sx] = to_bits(from_compute<ST>(perturbed(x, i, q)));
+                put(i, q, to_bits(from_compute<ST>(perturbed(x, i, q))));
             }
         }
     }
@@ -386,6 +426,7 @@ struct BatchedLaunch {
     bool vec_shapes;
     bool one_per_tile;
     const int32_t* order;   // one workgroup per tile: the plan's dispatch order, or NULL (runs of kOneTileRuns)
+    unsigned long long* bump;   // counter to increment, or NULL
 };
 
 template <typename ST, int P, int KIND>
@@ -400,7 +441,7 @@ hipError_t launch_batched(const BatchedLaunch& bl, const pw_domain_args* args, h
     if (attr_err != hipSuccess) return attr_err;
     hipLaunchKernelGGL(kern, dim3((unsigned)bl.workgroups), dim3(256), (size_t)bl.lds_bytes, stream, bl.table,
                        bl.ndomains, bl.tiles, args, bl.errors, bl.vec_shapes ? 1 : 0, bl.one_per_tile ? 1 : 0,
-                       bl.order, bl.gate);
+                       bl.order, bl.gate, bl.bump);
     return hipGetLastError();
 }
 
@@ -774,6 +815,51 @@ int32_t batched_plan_free(pw_plan* p) {
     return PW_OK;
 }
 
+// The advection of a batch; `bump` (or NULL): a counter the launch increments.
+static int32_t launch_advect(const pw_plan* plan, const pw_domain_args* d_args, unsigned long long* bump, hipStream_t s) {
+    const BatchState& B = plan->batch;
+    const BatchedLaunch bl{B.d_table, plan->ndomains, B.launch.tiles, B.launch.workgroups, B.launch.lds_bytes,
+                           B.d_errors, nullptr, B.vec_shapes, batched_one_per_tile(plan->tuning),
+                           B.d_order, bump};
+    const hipError_t e = dispatch_batched(plan->storage, B.launch.chunk, B.kind, bl, d_args, s);
+    return e == hipSuccess ? PW_OK : report_hip(e);
+}
+
+// The perturbation of a batch (HALO: and its halo fill), one workgroup per tile.
+template <bool HALO>
+static int32_t launch_perturb(const pw_plan* plan, const pw_domain_args* d_args, uint64_t seed,
+                              const unsigned long long* d_call, double amplitude, hipStream_t s) {
+    const Launch& L = plan->batch.launch;
+    if (L.tiles >= (int64_t(1) << 31)) return PW_ERR_UNSUPPORTED;
+    const dim3 grid((unsigned)L.tiles);
+    const BatchDomain* tb = plan->batch.d_table;
+    const int nd = plan->ndomains, ch = L.chunk;
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, tb, nd, ch, d_args, seed, d_call, amplitude);
+        return hipGetLastError();
+    };
+    hipError_t e = hipSuccess;
+    switch (plan->storage) {
+        case PW_F64: e = go(pw_perturb_kernel<double, HALO>); break;
+        case PW_F32: e = go(pw_perturb_kernel<float, HALO>); break;
+        case PW_BF16: e = go(pw_perturb_kernel<bf16_t, HALO>); break;
+        case PW_F16: e = go(pw_perturb_kernel<f16_t, HALO>); break;
+        case PW_I16: e = go(pw_perturb_kernel<fx16_t, HALO>); break;
+        case PW_I32: e = go(pw_perturb_kernel<fx32_t, HALO>); break;
+        default: return PW_ERR_UNSUPPORTED;
+    }
+    return e == hipSuccess ? PW_OK : report_hip(e);
+}
+
+// One timestep in two launches: perturbation with the halo fill, then the
+// advection, which also advances the call counter (the next step's
+// perturbation reads it after this launch).
+int32_t record_timestep(const pw_plan* plan, const pw_domain_args* d_args, uint64_t seed, unsigned long long* d_call,
+                        double amplitude, hipStream_t s) {
+    const int32_t rc = launch_perturb<true>(plan, d_args, seed, d_call, amplitude, s);
+    return rc == PW_OK ? launch_advect(plan, d_args, d_call, s) : rc;
+}
+
 }  // namespace pw
 
 using namespace pw;
@@ -785,13 +871,7 @@ int32_t pw_advect_batched(const pw_plan* plan, int32_t ndomains, const pw_domain
     if (ndomains != plan->ndomains) return PW_ERR_PLAN_MISMATCH;
     if (!plan->batch.d_table) return PW_ERR_UNSUPPORTED;
     if (elem_bytes(plan->storage) == 0) return PW_ERR_UNSUPPORTED;
-    const BatchState& B = plan->batch;
-    const BatchedLaunch bl{B.d_table, plan->ndomains, B.launch.tiles, B.launch.workgroups, B.launch.lds_bytes,
-                           B.d_errors, nullptr, B.vec_shapes, batched_one_per_tile(plan->tuning),
-                           B.d_order};
-    hipError_t e = dispatch_batched(plan->storage, B.launch.chunk, B.kind, bl, d_args, static_cast<hipStream_t>(stream));
-    if (e != hipSuccess) return report_hip(e);
-    return PW_OK;
+    return launch_advect(plan, d_args, nullptr, static_cast<hipStream_t>(stream));
 }
 
 int32_t pw_fill_halo_batched(const pw_plan* plan, int32_t ndomains, const pw_domain_args* d_args, void* stream) {
@@ -820,38 +900,11 @@ int32_t pw_perturb_batched(const pw_plan* plan, int32_t ndomains, const pw_domai
     if (!plan || !d_args || !d_call || !std::isfinite(amplitude)) return PW_ERR_INVALID_ARG;
     if (ndomains != plan->ndomains) return PW_ERR_PLAN_MISMATCH;
     if (!plan->batch.d_table) return PW_ERR_UNSUPPORTED;
-    const Launch& L = plan->batch.launch;
-    if (L.tiles >= (int64_t(1) << 31)) return PW_ERR_UNSUPPORTED;
-    const dim3 grid((unsigned)L.tiles);   // one workgroup per tile
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const BatchDomain* tb = plan->batch.d_table;
-    const int nd = plan->ndomains, ch = L.chunk;
-    switch (plan->storage) {
-        case PW_F64:
-            hipLaunchKernelGGL(pw_perturb_kernel<double>, grid, dim3(256), 0, s, tb, nd, ch, d_args, seed, d_call, amplitude);
-            break;
-        case PW_F32:
-            hipLaunchKernelGGL(pw_perturb_kernel<float>, grid, dim3(256), 0, s, tb, nd, ch, d_args, seed, d_call, amplitude);
-            break;
-        case PW_BF16:
-            hipLaunchKernelGGL(pw_perturb_kernel<bf16_t>, grid, dim3(256), 0, s, tb, nd, ch, d_args, seed, d_call, amplitude);
-            break;
-        case PW_F16:
-            hipLaunchKernelGGL(pw_perturb_kernel<f16_t>, grid, dim3(256), 0, s, tb, nd, ch, d_args, seed, d_call, amplitude);
-            break;
-        case PW_I16:
-            hipLaunchKernelGGL(pw_perturb_kernel<fx16_t>, grid, dim3(256), 0, s, tb, nd, ch, d_args, seed, d_call, amplitude);
-            break;
-        case PW_I32:
-            hipLaunchKernelGGL(pw_perturb_kernel<fx32_t>, grid, dim3(256), 0, s, tb, nd, ch, d_args, seed, d_call, amplitude);
-            break;
-        default: return PW_ERR_UNSUPPORTED;
-    }
-    hipError_t e = hipGetLastError();
-    if (e == hipSuccess) {
-        hipLaunchKernelGGL(pw_bump_kernel, dim3(1), dim3(1), 0, s, d_call);
-        e = hipGetLastError();
-    }
+    const int32_t rc = launch_perturb<false>(plan, d_args, seed, d_call, amplitude, s);
+    if (rc != PW_OK) return rc;
+    hipLaunchKernelGGL(pw_bump_kernel, dim3(1), dim3(1), 0, s, d_call);
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return report_hip(e);
     return PW_OK;
 }
@@ -1042,7 +1095,7 @@ int32_t pw_advect_batched_noalloc(int32_t storage, const pw_shape* shapes, int32
     unsigned long long* errors = d_skipped ? d_skipped : reinterpret_cast<unsigned long long*>(scr + 16);
     const BatchedLaunch bl{reinterpret_cast<const BatchDomain*>(scr + kNoAllocHeader), ndomains, L.tiles,
                            L.workgroups, L.lds_bytes, errors, reinterpret_cast<const uint32_t*>(scr), vec,
-                           batched_one_per_tile(t), nullptr};
+                           batched_one_per_tile(t), nullptr, nullptr};
     e = dispatch_batched(storage, L.chunk, kind, bl, d_args, st);
     if (e != hipSuccess) return report_hip(e);
     return PW_OK;

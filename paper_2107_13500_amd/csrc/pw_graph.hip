@@ -9,6 +9,7 @@
 // exactly the recorded work.
 #include <hip/hip_runtime.h>
 
+#include <cmath>
 #include <new>
 
 #include "pw_advect.h"
@@ -97,16 +98,14 @@ int32_t pw_graph_capture_timestep(const pw_plan* plan, int32_t ndomains, const p
                                   pw_graph** graph) {
     if (!graph) return PW_ERR_INVALID_ARG;
     *graph = nullptr;
-    if (!plan || !d_args || !d_call || nsteps < 1) return PW_ERR_INVALID_ARG;
+    if (!plan || !d_args || !d_call || nsteps < 1 || !std::isfinite(amplitude)) return PW_ERR_INVALID_ARG;
     if (ndomains != plan->ndomains) return PW_ERR_PLAN_MISMATCH;
     if (!plan->batch.d_table) return PW_ERR_UNSUPPORTED;
     void* s = nullptr;
     int32_t rc = pw_graph_begin(&s);
     if (rc != PW_OK) return rc;
     for (int32_t step = 0; step < nsteps && rc == PW_OK; ++step) {
-        rc = pw_perturb_batched(plan, ndomains, d_args, seed, d_call, amplitude, s);
-        if (rc == PW_OK) rc = pw_fill_halo_batched(plan, ndomains, d_args, s);
-        if (rc == PW_OK) rc = pw_advect_batched(plan, ndomains, d_args, s);
+        rc = pw::record_timestep(plan, d_args, seed, d_call, amplitude, static_cast<hipStream_t>(s));
     }
     if (rc == PW_OK) return pw_graph_end(s, graph);
     pw_graph* abandoned = nullptr;

@@ -84,5 +84,7 @@ int32_t report_hip(hipError_t e);
 // batched plans (pw_batched.hip)
 int32_t batched_plan_init(pw_plan* p);
 int32_t batched_plan_free(pw_plan* p);
+int32_t record_timestep(const pw_plan* plan, const pw_domain_args* d_args, uint64_t seed, unsigned long long* d_call,
+                        double amplitude, hipStream_t s);
 
 }  // namespace pw

@@ -105,3 +105,35 @@ def test_graph_entry_points_reject_bad_arguments():
     assert l.pw_graph_capture_timestep(plan.handle, 3, batch.d_args.data_ptr(), 1, batch.call.data_ptr(), 1e-3,
                                        1, ctypes.byref(g)) == -8   # ndomains differs from the plan
     assert not g.value
+
+
+@pytest.mark.parametrize("storage", [B.F64, B.F32, B.BF16, B.F16, B.I16, B.I32],
+                         ids=["f64", "f32", "bf16", "f16", "i16", "i32"])
+@pytest.mark.parametrize("tuning", [None, {"chunk": 256, "seg": 1}, {"chunk": 1024, "seg": 64, "wg_per_cu": 2}],
+                         ids=["default", "c256s1", "c1024s64w2"])
+def test_recorded_timestep_writes_every_halo_copy(storage, tuning):
+    """The recorded timestep writes the halo with the perturbation: domains one
+    and two columns wide (a column copied to both sides), one and two planes
+    deep, odd heights, chunks that end inside a column, tiles of one plane --
+    every array equals the three eager calls bit for bit, halos included."""
+    shapes = [(1, 1, 64), (1, 7, 64), (9, 1, 33), (2, 2, 5), (2, 13, 40), (17, 2, 96), (6, 19, 81)]
+    probs = [inputs.make_problem(nx, ny, nz, 1500 + d) for d, (nx, ny, nz) in enumerate(shapes)]
+    ga, eb = BT.DeviceBatch(probs, storage, DEV), BT.DeviceBatch(probs, storage, DEV)
+    for bt in (ga, eb):
+        for f in bt.fields:
+            for a in f[:3]:
+                for face in (a[0], a[-1], a[:, 0], a[:, -1]):
+                    face.fill_(3)      # stale halos
+    pa, pb = ga.plan(tuning), eb.plan(tuning)
+    g = ga.capture_timestep(pa, seed=21, amplitude=1e-2)
+    for r in range(2):
+        say("recorded halo", B.DTYPE_NAMES[storage], r)
+        g.launch()
+        eb.timestep(pb, seed=21, amplitude=1e-2)
+        torch.cuda.synchronize()
+        assert int(ga.call.item()) == r + 1
+        for d in range(len(probs)):
+            for f, (x, y) in enumerate(zip(ga.fields[d], eb.fields[d])):
+                assert torch.equal(x.contiguous().view(torch.uint8), y.contiguous().view(torch.uint8)), (r, d, f)
+    assert pa.error_count() == 0 and pb.error_count() == 0
+    g.close()
