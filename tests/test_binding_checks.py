@@ -48,3 +48,51 @@ def test_short_or_non_double_coefficients_are_refused():
 def test_host_tensors_are_refused_for_device_calls():
     with pytest.raises(ValueError, match="CUDA tensor"):
         B.check_fields(B.F64, SHAPE, fields(), coefs())
+
+
+class FakePlan:
+    storage = B.F64
+    shapes = [SHAPE]
+    _layout = None
+
+
+class OnDevice:
+    """A host tensor that reports a GPU device, so that the comparisons of a
+    device call can be checked without one."""
+
+    def __init__(self, t, dev=0):
+        self.t, self.dev, self.is_cuda = t, dev, dev >= 0
+        self.dtype, self.shape = t.dtype, t.shape
+        self.stride, self.numel, self.is_contiguous = t.stride, t.numel, t.is_contiguous
+
+    def get_device(self):
+        return self.dev
+
+
+def test_the_quick_check_refuses_whatever_check_fields_refuses():
+    """fields_fit accepts only what check_fields accepts: one wrong property in
+    any of the ten tensors makes it fall back to the naming check."""
+    good = [OnDevice(t) for t in fields()], [OnDevice(t) for t in coefs()]
+    assert B.fields_fit(FakePlan(), *good)
+    bad_fields = [torch.zeros(8, 7, 8, dtype=torch.float32), torch.zeros(7, 7, 8, dtype=torch.float64),
+                  torch.zeros(8, 7, 10, dtype=torch.float64)[:, :, :8], torch.zeros(8, 7, 16, dtype=torch.float64)[:, :, ::2],
+                  torch.zeros(8, 8, 7, dtype=torch.float64).transpose(1, 2), torch.zeros(8, 7, 8, 1, dtype=torch.float64)]
+    for i in range(6):
+        for t in bad_fields:
+            f = list(good[0])
+            f[i] = OnDevice(t)
+            assert not B.fields_fit(FakePlan(), f, good[1]), (i, t.shape, t.stride())
+        f = list(good[0])
+        f[i] = OnDevice(fields()[0], dev=1)
+        assert not B.fields_fit(FakePlan(), f, good[1])
+    for i in range(4):
+        for t in (torch.zeros(8, dtype=torch.float32), torch.zeros(7, dtype=torch.float64),
+                  torch.zeros(16, dtype=torch.float64)[::2]):
+            z = list(good[1])
+            z[i] = OnDevice(t)
+            assert not B.fields_fit(FakePlan(), good[0], z)
+        z = list(good[1])
+        z[i] = OnDevice(coefs()[0], dev=1)
+        assert not B.fields_fit(FakePlan(), good[0], z)
+    host = [OnDevice(t, dev=-1) for t in fields()], [OnDevice(t, dev=-1) for t in coefs()]
+    assert not B.fields_fit(FakePlan(), *host)
