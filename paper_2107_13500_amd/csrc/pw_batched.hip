@@ -315,8 +315,13 @@ __device__ __forceinline__ uint32_t lowbias32(uint32_t x) {
 // HALO (the recorded timestep): also the periodic halo of u, v, w, written
 // from the values in hand -- a boundary point's copies go out with it, only
 // w's boundary columns are read besides -- with the result of pw_halo_kernel
-// after this kernel.  On 384 domains the halo pass costs 84 us (FP32) by
-// itself, which reads again what this kernel has just written.
+// after this kernel, which would read again what this one has just written.
+// Bound by instruction issue (two 32-bit hashes per element, whose four
+// multiplications run at a quarter of the rate), then by the HBM: 384 domains
+// FP32 386 us with the halo (2.2 GB), against 355 + 84 us and a launch for the
+// counter; addresses advance by additions, and only waves with a boundary
+// column and groups with a boundary plane carry the copies' code (411 us with
+// it in every step).
 constexpr int kPerturbPlanes = 4;
 
 template <typename ST, bool HALO>
@@ -345,15 +350,13 @@ __global__ __launch_bounds__(256) void pw_perturb_kernel(const BatchDomain* __re
     global_ptr<U> f[3] = {as_global((U*)a.u), as_global((U*)a.v), as_global((U*)a.w)};
     const CT sc[2] = {static_cast<CT>(scaled_type<ST>::value ? scale_or_one(a.scales.in_scale[0]) : 1.0f),
                       static_cast<CT>(scaled_type<ST>::value ? scale_or_one(a.scales.in_scale[1]) : 1.0f)};
-    uint32_t p = 0;
-    // x + amp r (times the field's scale) at plane i of point p, field q
-    auto perturbed = [&](CT x, int i, int q) {
-        const uint32_t g = (uint32_t)(i - 1) * nyz + p;
-        const uint32_t h = lowbias32(key ^ lowbias32(2u * g + (uint32_t)q));
+    // x + amp r (times the field's scale) for the element whose hash index (2 g + q) is n
+    auto perturbed = [&](CT x, uint32_t n, int q) {
+        const uint32_t h = lowbias32(key ^ lowbias32(n));
         const float r = (float)(h >> 8) * 0x1.0p-23f - 1.0f;   // [-1, 1)
         return x + static_cast<CT>(amp * (double)r) * sc[q];
     };
-    for (p = (uint32_t)c * (uint32_t)chunk + threadIdx.x; p < pend; p += 256) {
+    for (uint32_t p = (uint32_t)c * (uint32_t)chunk + threadIdx.x; p < pend; p += 256) {
         const uint32_t k = p % nz;
         const uint32_t j = p / nz + 1;
         const int64_t col = k + (int64_t)j * b.sy;
@@ -375,40 +378,52 @@ __global__ __launch_bounds__(256) void pw_perturb_kernel(const BatchDomain* __re
                 across(g, plane, x);
             }
         };
-        auto put = [&](int i, int q, U x) {
-            f[q][col + (int64_t)i * b.sx] = x;
-            if (HALO) spread(f[q], i, x);
+        const int64_t step = b.sx;   // uniform
+        global_ptr<U> at[3];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) at[q] = f[q] + (col + (int64_t)i0 * step);
+        uint32_t n = 2u * ((uint32_t)(i0 - 1) * nyz + p);
+        // N planes from plane i on: all their loads first (unconditional, so
+        // they are in flight together), then the results.  EDGE: with halo copies.
+        auto group = [&](auto count, auto edge, int i) {
+            constexpr int N = decltype(count)::value;
+            constexpr bool EDGE = decltype(edge)::value;
+            CT x[N][2];
+            U w[N];
+#pragma unroll
+            for (int u = 0; u < N; ++u) {
+#pragma unroll
+                for (int q = 0; q < 2; ++q) x[u][q] = to_compute(from_bits<ST>(at[q][u * step]));
+                if (EDGE) w[u] = at[2][u * step];
+            }
+#pragma unroll
+            for (int u = 0; u < N; ++u) {
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    const U y = to_bits(from_compute<ST>(perturbed(x[u][q], n + 2u * (uint32_t)u * nyz + (uint32_t)q, q)));
+                    at[q][u * step] = y;
+                    if (EDGE) spread(f[q], i + u, y);
+                }
+                if (EDGE) spread(f[2], i + u, w[u]);
+            }
+#pragma unroll
+            for (int q = 0; q < 3; ++q) at[q] += N * step;
+            n += 2u * N * nyz;
         };
-        if (HALO) {
-            if (to_lo || to_hi) {
-                for (int i = i0; i <= i1; ++i) spread(f[2], i, f[2][col + (int64_t)i * b.sx]);
-            } else {
-                if (i0 == 1) spread(f[2], 1, f[2][col + b.sx]);
-                if (i1 == b.nx && (b.nx > 1 || i0 != 1)) spread(f[2], b.nx, f[2][col + (int64_t)b.nx * b.sx]);
-            }
-        }
-        // full groups of kPerturbPlanes planes without conditions (so the
-        // compiler keeps all their loads in flight), then the rest one by one
+        // waves that hold a boundary column, and groups that hold the first
+        // or the last plane, write halo copies
+        const bool side = HALO && __ballot(to_lo || to_hi) != 0ull;
+        auto run = [&](auto count, int i) {
+            constexpr int N = decltype(count)::value;
+            if (HALO && (side || i == 1 || i + N - 1 == b.nx)) group(count, std::true_type{}, i);
+            else group(count, std::false_type{}, i);
+        };
         int i = i0;
-        for (; i + kPerturbPlanes - 1 <= i1; i += kPerturbPlanes) {
-            CT x[kPerturbPlanes][2];
-#pragma unroll
-            for (int u = 0; u < kPerturbPlanes; ++u)
-#pragma unroll
-                for (int q = 0; q < 2; ++q) x[u][q] = to_compute(from_bits<ST>(f[q][col + (int64_t)(i + u) * b.sx]));
-#pragma unroll
-            for (int u = 0; u < kPerturbPlanes; ++u)
-#pragma unroll
-                for (int q = 0; q < 2; ++q)
-                    put(i + u, q, to_bits(from_compute<ST>(perturbed(x[u][q], i + u, q))));
-        }
-        for (; i <= i1; ++i) {
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                const CT x = to_compute(from_bits<ST>(f[q][col + (int64_t)i * b.sx]));
-                put(i, q, to_bits(from_compute<ST>(perturbed(x, i, q))));
-            }
-        }
+        for (; i + kPerturbPlanes - 1 <= i1; i += kPerturbPlanes) run(std::integral_constant<int, kPerturbPlanes>{}, i);
+        static_assert(kPerturbPlanes == 4, "remainders of one to three planes");
+        if (i + 2 == i1) run(std::integral_constant<int, 3>{}, i);
+        else if (i + 1 == i1) run(std::integral_constant<int, 2>{}, i);
+        else if (i == i1) run(std::integral_constant<int, 1>{}, i);
     }
 }
 
