@@ -165,12 +165,16 @@ int32_t auto_seg(int32_t storage, const pw_shape& s, int32_t nchunks, int64_t ld
 // of 1, 2, 4, 8, 16, 32 on grids from 5 to 74 million points (250 x 310 x 60
 // padded FP64: 58 us with 4, 64 with 8, 77 with 1; 500 x 500 x 199 padded
 // BF16: 230 with 8, 234 with 4, 390 with 1), 2 on grids that do not fill the
-// chip (kWaves waves in flight).  FP64 compute on large grids takes
-// workgroups of 512 threads, whose eight waves share more rows (58 against
-// 61 us; 512 x 512 x 64: 181 against 195); the others 256.
+// chip (kWaves waves in flight).  Large grids take workgroups of 512 threads,
+// whose eight waves share more rows: FP64 from 4 million points on (250 x 310 x
+// 60 padded 58 against 61 us, 512 x 512 x 64 181 against 195), int32 and the
+// 16-bit types from 16 million on (500 x 500 x 199 padded int32 388 against
+// 421 us, BF16 230 against 246; 250 x 310 x 60 int32 32 against 29, hence the
+// line); FP32 is indifferent (404 against 400 us) and keeps 256.
 static int32_t direct_block(int32_t storage, const pw_shape& s) {
-    const int64_t pairs = (int64_t)s.ny * (((int64_t)s.nz + 1) / 2);
-    return compute_bytes(storage) == 8 && pairs * s.nx >= (int64_t(1) << 21) ? 512 : 256;
+    const int64_t pairs = (int64_t)s.ny * (((int64_t)s.nz + 1) / 2) * s.nx;
+    if (storage == PW_F32) return 256;
+    return pairs >= (int64_t(1) << (storage == PW_F64 ? 21 : 23)) ? 512 : 256;
 }
 static int32_t direct_seg(int32_t storage, const pw_shape& s, int32_t nchunks, int32_t block) {
     constexpr int64_t kWaves = 256 * 12;

@@ -824,7 +824,8 @@ struct MarchTile {
         // the rounds of some waves first, so that the waits of the others
         // count the loads after theirs exactly
 #pragma unroll
-        for (int r = NVR - 1; r >= 0; --r) {
+        for (int v = 0; v < NVR; ++v) {
+            const int r = EXACT && NFULL < NVR ? NVR - 1 - v : v;
             if (EXACT ? r < NFULL || more[r] : fsel[r] >= 0) dst[r] = load_global<Raw, RAW_ALIGN>(gp[r]);
             gp[r] += ps;
         }
@@ -1083,8 +1084,9 @@ __device__ __forceinline__ bool single_tile(const MarchGeom& g, int nx, int& c, 
     const int tile = g.run > 0 ? march_compact_tile((int)blockIdx.x, g.nchunks * g.nseg, g.run, g.blocks)
                                : xcd_tile((int)blockIdx.x, (int)gridDim.x);
     if (tile < 0) return false;   // whole workgroup
-    c = tile % g.nchunks;
-    i_begin = 1 + tile / g.nchunks * g.seg;
+    const int s = tile / g.nchunks;
+    c = tile - s * g.nchunks;
+    i_begin = 1 + s * g.seg;
     i_end = min(i_begin + g.seg - 1, nx);
     return true;
 }
