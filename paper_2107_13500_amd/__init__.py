@@ -10,7 +10,7 @@ __all__ = ["inputs", "metrics", "binding"]
 
 
 #: sources the single-domain kernels are compiled from
-KERNEL_SOURCES = ("pw_types.hpp", "pw_stencil.hpp", "pw_kernels.hpp", "pw_plan.hpp", "pw_advect.hip")
+KERNEL_SOURCES = ("pw_types.hpp", "pw_stencil.hpp", "pw_tiles.hpp", "pw_kernels.hpp", "pw_plan.hpp", "pw_advect.hip")
 
 
 def _strip_comments(text: str) -> str:

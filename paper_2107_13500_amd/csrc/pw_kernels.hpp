@@ -24,6 +24,7 @@
 #include <type_traits>
 
 #include "pw_stencil.hpp"
+#include "pw_tiles.hpp"
 
 namespace pw {
 
@@ -682,7 +683,7 @@ struct MarchTile {
 
     const DomainArgs& d;
     CT* lds;
-    int nz_rt, wb, wlen, pend;
+    int nz_rt, wb, wlen;
     int li[PPT];
     int kk[PPT];
     bool live[PPT];          // point lies in the chunk (always true when CLAMP)
@@ -737,12 +738,8 @@ struct MarchTile {
 
     __device__ __forceinline__ MarchTile(const DomainArgs& dd, int c, CT* l) : d(dd), lds(l), nz_rt(dd.nz) {
         const int n = nz();
-        int p0 = n + c * P;                             // first point of the chunk (j >= 1)
-        pend = min(p0 + P, (d.ny + 1) * n);             // one past the last interior point
-        // a pair needs two points: a last chunk of one starts a point early
-        // (never the only chunk, which has at least nz >= 2)
-        if (ANY && PAIR && pend - p0 == 1) --p0;
-        wb = p0 - n;                                    // window start: one column of y halo
+        const ChunkSpan cs = chunk_span(c, P, d.ny, n, ANY && PAIR);
+        wb = cs.first - n;                              // window start: one column of y halo
         wlen = min(P + 2 * n, (d.ny + 2) * n - wb);
         const int nvec = (wlen + VW - 1) / VW;   // vectors per field (wlen >= 5 >= VW; NZ > 0: a multiple of VW)
 #pragma unroll
@@ -764,14 +761,14 @@ struct MarchTile {
 #pragma unroll
         for (int q = 0; q < PPT; ++q) {
             const int t = (int)threadIdx.x;
-            int p = PAIR ? p0 + 2 * (t + NT * (q / 2)) + (q % 2) : p0 + t + NT * q;
+            int p = PAIR ? 2 * (t + NT * (q / 2)) + (q % 2) : t + NT * q;   // relative to cs.first
             // CLAMP: points past the chunk's end (last chunk of a domain)
             // recompute the chunk's last point or pair and store the
             // identical result again, so stores need no branch either.
-            if (CLAMP) p = PAIR ? min(p, pend - 2 + (q % 2)) : min(p, pend - 1);
-            live[q] = p < pend;
-            kk[q] = p % n + 1;
-            li[q] = p - wb;
+            if (CLAMP) p = PAIR ? min(p, cs.count - 2 + (q % 2)) : min(p, cs.count - 1);
+            live[q] = p < cs.count;
+            kk[q] = point_level(cs.first, p, n);
+            li[q] = p + n;
             const PointCoefs<CT> c = point_coefs<ST>(d, live[q] ? kk[q] : 1);
             zc[q][0] = c.z1u;
             zc[q][1] = c.z2u;

@@ -1,0 +1,57 @@
+"""The kernels' tile arithmetic (csrc/pw_tiles.hpp) on the CPU, at the limits
+of the shapes a plan accepts: compiled with the host compiler and compared
+with Python integers."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+from paper_2107_13500_amd import build as hipbuild
+
+WRAPPERS = """
+#include "pw_tiles.hpp"
+extern "C" {
+void span(int32_t c, int32_t p, int32_t ny, int32_t nz, int32_t pairs, int32_t* out) {
+    const pw::ChunkSpan s = pw::chunk_span(c, p, ny, nz, pairs != 0);
+    out[0] = s.first;
+    out[1] = s.count;
+}
+int32_t level(int32_t first, int32_t rel, int32_t nz) { return pw::point_level(first, rel, nz); }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def tiles(tmp_path_factory):
+    d = tmp_path_factory.mktemp("tiles")
+    src, lib = os.path.join(str(d), "tiles.cpp"), os.path.join(str(d), "tiles.so")
+    with open(src, "w") as f:
+        f.write(WRAPPERS)
+    subprocess.run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__host__=", "-D__device__=",
+                    "-I", hipbuild.CSRC, src, "-o", lib], check=True)
+    return ctypes.CDLL(lib)
+
+
+def largest_ny(nz):
+    """Rows of the largest plane a plan accepts: (ny + 2) nz < 2^31."""
+    return (2 ** 31 - 1) // nz - 2
+
+
+@pytest.mark.parametrize("chunk", [256, 512, 1024])
+@pytest.mark.parametrize("nz", [2, 3, 64, 65, 96, 128, 255, 256])
+def test_chunks_of_the_largest_planes_stay_inside_them(tiles, chunk, nz):
+    out = (ctypes.c_int32 * 2)()
+    for ny in (1, 7, 513, largest_ny(nz) - 1, largest_ny(nz)):
+        points = ny * nz
+        nchunks = -(-points // chunk)
+        for c in {0, nchunks // 2, max(0, nchunks - 2), nchunks - 1}:
+            for pairs in (0, 1):
+                tiles.span(c, chunk, ny, nz, pairs, out)
+                first, count = nz + c * chunk, min(chunk, points - c * chunk)
+                if pairs and count == 1:
+                    first, count = first - 1, 2
+                assert tuple(out) == (first, count), (ny, c, pairs)
+                assert first - nz >= 0 and first + count <= (ny + 1) * nz
+                for rel in (0, count - 1, chunk - 1):   # lanes past the end of the chunk too
+                    assert tiles.level(first, rel, nz) == (first + rel) % nz + 1
