@@ -601,17 +601,16 @@ int64_t halo_blocks(const pw_plan* p) {
 }  // namespace
 
 // Tile split of one domain: nchunks chunks of `chunk` points per plane, x
-// range split into nseg segments of even length (at most seg_max planes:
-// nseg = ceil(nx / seg_max) parts of ceil(nx / nseg) planes, which start at or
-// before plane nx and cover every plane).
+// range split into nseg segments of even length (at most seg_max planes).
 __host__ __device__ inline void domain_tiles(int32_t nx, int32_t ny, int32_t nz, int32_t chunk, int32_t seg_max,
                                              BatchDomain* b) {
     b->nx = nx;
     b->ny = ny;
     b->nz = nz;
     b->nchunks = (int32_t)(((int64_t)ny * nz + chunk - 1) / chunk);
-    b->nseg = (nx + seg_max - 1) / seg_max;
-    b->seg = (nx + b->nseg - 1) / b->nseg;
+    const SegmentSplit x = segment_split(nx, seg_max);
+    b->nseg = x.n;
+    b->seg = x.len;
 }
 
 // Launch shape of the batched kernel for a list of (normalised) shapes:

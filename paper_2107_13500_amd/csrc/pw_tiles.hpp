@@ -27,4 +27,16 @@ __host__ __device__ inline int32_t point_level(int32_t first, int32_t rel, int32
     return (int32_t)(((uint32_t)first + (uint32_t)rel) % (uint32_t)nz) + 1;
 }
 
+// Split of nx planes into segments of at most `most` planes (any positive
+// value): n = ceil(nx / most) segments of len = ceil(nx / n) planes, which
+// start at or before plane nx and cover every plane (the last may be shorter).
+struct SegmentSplit {
+    int32_t n, len;
+};
+__host__ __device__ inline SegmentSplit segment_split(int32_t nx, int32_t most) {
+    const int64_t m = most < nx ? most : nx;
+    const int64_t n = (nx + m - 1) / m;
+    return SegmentSplit{(int32_t)n, (int32_t)((nx + n - 1) / n)};
+}
+
 }  // namespace pw

@@ -375,3 +375,36 @@ def test_default_segments_of_batches_of_any_size(storage, shapes):
     for a, b in zip(*got):
         for x, y in zip(a, b):
             assert same_bits(x, y) if storage != B.I16 else torch.equal(x, y)
+
+
+def test_a_segment_bound_beyond_every_domain_means_whole_domains():
+    """seg up to the largest int32: one segment per domain, the plan's and the
+    plan-less launch alike, the bits of an explicit bound of the longest domain."""
+    probs = small_problems(SMALL, seed=445)
+    batch = BT.DeviceBatch(probs, B.F64, DEV)
+    whole = max(s[0] for s in SMALL)
+    want = batch.plan({"seg": whole})
+    batch.advect(want)
+    torch.cuda.synchronize()
+    ref = [[o.clone() for o in f[3:]] for f in batch.fields]
+    for seg in (2 ** 31 - 1, 2 ** 30):
+        plan = batch.plan({"seg": seg})
+        assert plan.info()["tiles"] == want.info()["tiles"]
+        assert plan.info()["workgroups"] == want.info()["workgroups"]
+        single = B.Plan(B.F64, [batch.shapes[4]], {"seg": seg})   # a single domain's plan holds a batched table too
+        assert single.info()["batched_workgroups"] == 64          # 6 chunks in one segment, padded to a block
+        for noalloc in (False, True):
+            say("segment bound", seg, noalloc)
+            for f in batch.fields:
+                for o in f[3:]:
+                    o.zero_()
+            if noalloc:
+                skipped = torch.zeros(1, dtype=torch.int64, device=DEV)
+                B.advect_batched_noalloc(B.F64, batch.shapes, batch.d_args, {"seg": seg}, skipped)
+            else:
+                batch.advect(plan)
+            torch.cuda.synchronize()
+            assert (int(skipped.item()) if noalloc else plan.error_count()) == 0
+            for a, f in zip(ref, batch.fields):
+                for x, y in zip(a, f[3:]):
+                    assert same_bits(x, y)

@@ -17,6 +17,11 @@ void span(int32_t c, int32_t p, int32_t ny, int32_t nz, int32_t pairs, int32_t* 
     out[0] = s.first;
     out[1] = s.count;
 }
+void split(int32_t nx, int32_t most, int32_t* out) {
+    const pw::SegmentSplit s = pw::segment_split(nx, most);
+    out[0] = s.n;
+    out[1] = s.len;
+}
 int32_t level(int32_t first, int32_t rel, int32_t nz) { return pw::point_level(first, rel, nz); }
 }
 """
@@ -55,3 +60,13 @@ def test_chunks_of_the_largest_planes_stay_inside_them(tiles, chunk, nz):
                 assert first - nz >= 0 and first + count <= (ny + 1) * nz
                 for rel in (0, count - 1, chunk - 1):   # lanes past the end of the chunk too
                     assert tiles.level(first, rel, nz) == (first + rel) % nz + 1
+
+
+@pytest.mark.parametrize("most", [1, 2, 7, 16, 64, 2 ** 30, 2 ** 31 - 2, 2 ** 31 - 1])
+def test_segments_cover_every_plane_for_any_bound(tiles, most):
+    out = (ctypes.c_int32 * 2)()
+    for nx in (1, 2, 3, 16, 17, 64, 1000, 2 ** 30 - 1, 2 ** 30):
+        tiles.split(nx, most, out)
+        n, length = out
+        assert 1 <= length <= most and n >= 1
+        assert (n - 1) * length < nx <= n * length, (nx, n, length)
