@@ -252,27 +252,13 @@ __global__ __launch_bounds__(256) void pw_halo_kernel(const BatchDomain* __restr
     const BatchDomain b = table[blockIdx.y];
     const pw_domain_args& a = args[b.rec];
     if (!shape_matches(a.shape, b)) return;
-    const int nhalo = 2 * (b.nx + 2) + 2 * b.ny;
     using U = storage_bits<ST>;
     global_ptr<U> f[3] = {as_global((U*)a.u), as_global((U*)a.v), as_global((U*)a.w)};
-    const int64_t n = (int64_t)nhalo * b.nz;
+    const int64_t n = halo_columns(b.nx, b.ny) * b.nz;
     for (int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x; g < n; g += (int64_t)gridDim.x * 256) {
         const int k = (int)(g % b.nz);
-        const int h = (int)(g / b.nz);
-        int i, j;
-        if (h < b.nx + 2) {
-            i = h;
-            j = 0;
-        } else if (h < 2 * (b.nx + 2)) {
-            i = h - (b.nx + 2);
-            j = b.ny + 1;
-        } else if (h < 2 * (b.nx + 2) + b.ny) {
-            i = 0;
-            j = 1 + h - 2 * (b.nx + 2);
-        } else {
-            i = b.nx + 1;
-            j = 1 + h - 2 * (b.nx + 2) - b.ny;
-        }
+        const Column at = halo_column((uint32_t)(g / b.nz), b.nx, b.ny);
+        const int i = at.i, j = at.j;
         const int si = i == 0 ? b.nx : (i == b.nx + 1 ? 1 : i);
         const int sj = j == 0 ? b.ny : (j == b.ny + 1 ? 1 : j);
         const int64_t dst = k + (int64_t)j * b.sy + (int64_t)i * b.sx;
@@ -586,16 +572,17 @@ hipError_t dispatch_batched(int32_t storage, int32_t chunk, int32_t kind, const 
 }
 
 // Workgroups per domain of the halo fill: the mean domain's halo in blocks
-// of 256 elements (larger domains loop), at most the largest domain's.
+// of 256 elements (larger domains loop), at most the largest domain's and a
+// million.
 int64_t halo_blocks(const pw_plan* p) {
     int64_t m = 0, sum = 0;
     for (const pw_shape& s : p->shapes) {
-        const int64_t e = (int64_t)(2 * (s.nx + 2) + 2 * s.ny) * s.nz;
+        const int64_t e = halo_columns(s.nx, s.ny) * s.nz;
         m = std::max<int64_t>(m, e);
         sum += e;
     }
     const int64_t mean = sum / std::max<int64_t>(1, (int64_t)p->shapes.size());
-    return std::max<int64_t>(1, std::min((m + 255) / 256, (mean + 255) / 256));
+    return std::max<int64_t>(1, std::min<int64_t>({(m + 255) / 256, (mean + 255) / 256, int64_t(1) << 20}));
 }
 
 }  // namespace

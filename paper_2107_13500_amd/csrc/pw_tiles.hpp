@@ -39,4 +39,23 @@ __host__ __device__ inline SegmentSplit segment_split(int32_t nx, int32_t most) 
     return SegmentSplit{(int32_t)n, (int32_t)((nx + n - 1) / n)};
 }
 
+// Columns of the one-point x-y halo around nx x ny interior columns: up to
+// 2^31 + 4 for the domains of a batch (nx ny < 2^30).
+__host__ __device__ inline int64_t halo_columns(int32_t nx, int32_t ny) {
+    return 2 * ((int64_t)nx + 2) + 2 * (int64_t)ny;
+}
+
+// Halo column h: first the rows j = 0 and j = ny + 1 over i = 0 .. nx + 1,
+// then the planes i = 0 and i = nx + 1 over j = 1 .. ny.
+struct Column {
+    int32_t i, j;
+};
+__host__ __device__ inline Column halo_column(uint32_t h, int32_t nx, int32_t ny) {
+    const uint32_t row = (uint32_t)nx + 2u, col = (uint32_t)ny;
+    if (h < row) return Column{(int32_t)h, 0};
+    if (h < 2u * row) return Column{(int32_t)(h - row), ny + 1};
+    if (h < 2u * row + col) return Column{0, 1 + (int32_t)(h - 2u * row)};
+    return Column{nx + 1, 1 + (int32_t)(h - 2u * row - col)};
+}
+
 }  // namespace pw

@@ -22,6 +22,12 @@ void split(int32_t nx, int32_t most, int32_t* out) {
     out[0] = s.n;
     out[1] = s.len;
 }
+int64_t halo(int32_t nx, int32_t ny) { return pw::halo_columns(nx, ny); }
+void column(uint32_t h, int32_t nx, int32_t ny, int32_t* out) {
+    const pw::Column c = pw::halo_column(h, nx, ny);
+    out[0] = c.i;
+    out[1] = c.j;
+}
 int32_t level(int32_t first, int32_t rel, int32_t nz) { return pw::point_level(first, rel, nz); }
 }
 """
@@ -35,7 +41,10 @@ def tiles(tmp_path_factory):
         f.write(WRAPPERS)
     subprocess.run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__host__=", "-D__device__=",
                     "-I", hipbuild.CSRC, src, "-o", lib], check=True)
-    return ctypes.CDLL(lib)
+    t = ctypes.CDLL(lib)
+    t.halo.restype = ctypes.c_int64
+    t.column.argtypes = [ctypes.c_uint32, ctypes.c_int32, ctypes.c_int32, ctypes.c_void_p]
+    return t
 
 
 def largest_ny(nz):
@@ -70,3 +79,27 @@ def test_segments_cover_every_plane_for_any_bound(tiles, most):
         n, length = out
         assert 1 <= length <= most and n >= 1
         assert (n - 1) * length < nx <= n * length, (nx, n, length)
+
+
+def test_halo_columns_are_each_counted_once(tiles):
+    out = (ctypes.c_int32 * 2)()
+    for nx, ny in ((1, 1), (1, 5), (6, 1), (7, 4)):
+        n = tiles.halo(nx, ny)
+        seen = set()
+        for h in range(n):
+            tiles.column(h, nx, ny, out)
+            seen.add(tuple(out))
+        want = {(i, j) for i in range(nx + 2) for j in range(ny + 2) if i in (0, nx + 1) or j in (0, ny + 1)}
+        assert seen == want and n == len(want)
+
+
+@pytest.mark.parametrize("nx,ny", [(2 ** 30 - 1, 1), (1, 2 ** 30 - 1), (2 ** 29, 2)])
+def test_halo_columns_of_the_longest_domains(tiles, nx, ny):
+    """Domains of nearly 2^31 points two levels deep: the count passes 2^31."""
+    out = (ctypes.c_int32 * 2)()
+    n = tiles.halo(nx, ny)
+    assert n == 2 * (nx + 2) + 2 * ny
+    for h, want in ((nx + 1, (nx + 1, 0)), (2 * nx + 3, (nx + 1, ny + 1)), (n - 1, (nx + 1, ny)),
+                    (n - 1 - ny, (0, ny))):
+        tiles.column(h, nx, ny, out)
+        assert tuple(out) == want
