@@ -122,7 +122,7 @@ struct SegModel {
     double idle, tail, rounds;
 };
 
-int32_t auto_seg(int32_t storage, const pw_shape& s, int32_t nchunks, int64_t lds_bytes) {
+static int32_t model_seg(int32_t storage, const pw_shape& s, int32_t nchunks, int64_t lds_bytes) {
     constexpr int kCus = 256;
     // FP64 heights of a class: a longer best length (382 x 317 x 113: 20 planes
     // 138 us, 6 planes 151 us)
@@ -157,6 +157,13 @@ int32_t auto_seg(int32_t storage, const pw_shape& s, int32_t nchunks, int64_t ld
     return best;
 }
 
+// The model's segments, longer where they are more than a launch may hold.
+int32_t auto_seg(int32_t storage, const pw_shape& s, int32_t nchunks, int64_t lds_bytes) {
+    int32_t seg = model_seg(storage, s, nchunks, lds_bytes);
+    while ((int64_t)nchunks * (((int64_t)s.nx + seg - 1) / seg) > kMaxTiles) seg = even_seg(s.nx, 2 * (int64_t)seg);
+    return seg;
+}
+
 // Default workgroup and planes per segment of the direct variant.  A wave
 // carries its planes from step to step, so segments only have to be long
 // enough to spread the two extra planes of their start, and short ones keep
@@ -181,7 +188,8 @@ static int32_t direct_seg(int32_t storage, const pw_shape& s, int32_t nchunks, i
     const int64_t most = compute_bytes(storage) == 8 ? 4 : 8;
     int64_t seg = (int64_t)nchunks * (block / 64) * s.nx / kWaves;
     seg = std::max<int64_t>(2, std::min<int64_t>(seg, most));
-    while ((int64_t)nchunks * ((s.nx + seg - 1) / seg) >= (int64_t(1) << 30)) seg *= 2;   // the grid's limit
+    // the grid's limit: fewer than 2^32 threads
+    while (seg < s.nx && (int64_t)nchunks * ((s.nx + seg - 1) / seg) * block >= (int64_t(1) << 32)) seg *= 2;
     return even_seg(s.nx, seg);
 }
 

@@ -641,11 +641,21 @@ int32_t batched_launch_shape(int32_t storage, const pw_shape* shapes, int32_t n,
     if (e != hipSuccess) return report_hip(e);
     int64_t per_cu = resident_per_cu(storage, chunk, k, r.lds_bytes);
     r.seg = t.seg ? t.seg : batched_seg(storage, planes, (int64_t)cus * std::min<int64_t>(per_cu, 4), sorted);
-    int64_t tiles = 0;
-    for (int32_t d = 0; d < n; ++d) {
-        BatchDomain b{};
-        domain_tiles(shapes[d].nx, shapes[d].ny, shapes[d].nz, chunk, r.seg, &b);
-        tiles += (int64_t)b.nchunks * b.nseg;
+    auto count = [&] {
+        int64_t tiles = 0;
+        for (int32_t d = 0; d < n; ++d) {
+            BatchDomain b{};
+            domain_tiles(shapes[d].nx, shapes[d].ny, shapes[d].nz, chunk, r.seg, &b);
+            tiles += (int64_t)b.nchunks * b.nseg;
+        }
+        return tiles;
+    };
+    int64_t tiles = count();
+    // a default segment length never makes more tiles than a launch may hold
+    // (unless whole domains do)
+    while (!t.seg && tiles > kMaxTiles && r.seg < (1 << 30)) {
+        r.seg *= 2;
+        tiles = count();
     }
     r.tiles = tiles;
     if (t.wg_per_cu > 0) per_cu = std::min<int64_t>(per_cu, t.wg_per_cu);
@@ -771,7 +781,7 @@ int32_t batched_plan_init(pw_plan* p) {
         // workgroups one XCD keeps resident: its CUs times the occupancy
         const int64_t per_cu = resident_per_cu(p->storage, L.chunk, kind, L.lds_bytes);
         order = one_tile_order(table, L.chunk, std::max<int64_t>(1, cus / kNumXcd) * per_cu);
-        if ((int64_t)order.size() >= (int64_t(1) << 31)) order.clear();
+        if ((int64_t)order.size() > kMaxTiles) order.clear();   // one long queue: the grid would not fit a launch
         if (!order.empty()) L.workgroups = (int64_t)order.size();
     }
     void* mem = nullptr;

@@ -40,6 +40,9 @@ __host__ __device__ constexpr int height_class(int nz) { return nz <= kHeightCla
 constexpr bool compiled_height(int nz) { return nz == 64 || nz == 96 || nz == 128; }
 constexpr int kLdsPerCu = 160 * 1024;           // gfx950 LDS per CU (and per workgroup)
 constexpr int kMaxDynamicLds = kLdsPerCu - 1024;   // leaves room for a kernel's small static LDS
+// A launch holds fewer than 2^32 threads: workgroups of 256, a block of 64 of
+// them left for the padding of the tile orders.
+constexpr int64_t kMaxTiles = (int64_t(1) << 24) - 64;
 constexpr int kNumXcd = 8;         // MI355X: 8 accelerator complex dies, one L2 each
 
 // Everything a kernel needs about one domain (passed by value).

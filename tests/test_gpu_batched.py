@@ -408,3 +408,15 @@ def test_a_segment_bound_beyond_every_domain_means_whole_domains():
             for a, f in zip(ref, batch.fields):
                 for x, y in zip(a, f[3:]):
                     assert same_bits(x, y)
+
+
+@pytest.mark.parametrize("storage", [B.F64, B.F32, B.BF16, B.I16, B.I32], ids=["f64", "f32", "bf16", "i16", "i32"])
+@pytest.mark.parametrize("shape", [(2 ** 29, 1, 2), (2 ** 28 - 1, 3, 2), (65535, 1, 16000)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_default_segments_keep_launches_below_2_to_the_32_threads(storage, shape):
+    """Very long domains of few columns: the default segments grow where their
+    tiles would be more than one launch may hold (plans only, nothing runs)."""
+    i = B.Plan(storage, [B.PwShape(*shape, 0, 0, 0)]).info()
+    say("long domain", B.DTYPE_NAMES[storage], shape, i)
+    assert 0 < i["workgroups"] * i["block"] < 2 ** 32
+    assert 0 <= i["batched_workgroups"] * 256 < 2 ** 32
