@@ -331,7 +331,8 @@ int32_t pw_graph_end(void *stream, pw_graph **graph);
 /* Record `nsteps` repeated timesteps of a batched plan into a new graph --
    each step the work of pw_perturb_batched (seed, d_call, amplitude), then
    pw_fill_halo_batched, then pw_advect_batched, all on `d_args`, in two
-   launches with the results of those three calls -- through
+   launches with the results of those three calls (one record may give one
+   array for several of u, v, w; u and v belong to no other record) -- through
    pw_graph_begin / pw_graph_end (allocates the graph; not for use while
    another recording of this thread is open).  Arguments as for those calls; nsteps >= 1.
    `graph` (host out-pointer) receives the graph. */

@@ -342,6 +342,7 @@ __global__ __launch_bounds__(256) void pw_perturb_kernel(const BatchDomain* __re
         const float r = (float)(h >> 8) * 0x1.0p-23f - 1.0f;   // [-1, 1)
         return x + static_cast<CT>(amp * (double)r) * sc[q];
     };
+    const bool own_w = a.w != a.u && a.w != a.v;   // else its halo goes out with u's or v's
     for (uint32_t p = (uint32_t)c * (uint32_t)chunk + threadIdx.x; p < pend; p += 256) {
         const uint32_t k = p % nz;
         const uint32_t j = p / nz + 1;
@@ -390,7 +391,7 @@ __global__ __launch_bounds__(256) void pw_perturb_kernel(const BatchDomain* __re
                     at[q][u * step] = y;
                     if (EDGE) spread(f[q], i + u, y);
                 }
-                if (EDGE) spread(f[2], i + u, w[u]);
+                if (EDGE && own_w) spread(f[2], i + u, w[u]);
             }
 #pragma unroll
             for (int q = 0; q < 3; ++q) at[q] += N * step;

@@ -137,3 +137,27 @@ def test_recorded_timestep_writes_every_halo_copy(storage, tuning):
                 assert torch.equal(x.contiguous().view(torch.uint8), y.contiguous().view(torch.uint8)), (r, d, f)
     assert pa.error_count() == 0 and pb.error_count() == 0
     g.close()
+
+
+@pytest.mark.parametrize("shared", [0, 1], ids=["w-is-u", "w-is-v"])
+def test_recorded_timestep_where_w_is_also_u_or_v(shared):
+    """A record may give one array for two fields: w's halo then holds the
+    perturbed values, as after the three eager calls."""
+    shapes = [(1, 1, 64), (9, 7, 64), (5, 2, 33), (20, 31, 96)]
+    probs = [inputs.make_problem(nx, ny, nz, 1600 + d) for d, (nx, ny, nz) in enumerate(shapes)]
+    ga, eb = BT.DeviceBatch(probs, B.F64, DEV), BT.DeviceBatch(probs, B.F64, DEV)
+    for bt in (ga, eb):
+        for f in bt.fields:
+            f[2] = f[shared]
+        bt.records = [B.domain_record(*f, p.coeffs.tcx, p.coeffs.tcy, *tz, scales=sc)
+                      for f, p, tz, sc in zip(bt.fields, probs, bt.tz, bt.scales)]
+        bt.d_args = B.domain_args_tensor(bt.records, DEV)
+    pa, pb = ga.plan(), eb.plan()
+    g = ga.capture_timestep(pa, seed=23, amplitude=1e-2)
+    for r in range(2):
+        say("shared field", shared, r)
+        g.launch()
+        eb.timestep(pb, seed=23, amplitude=1e-2)
+        torch.cuda.synchronize()
+        assert_same_state(ga, eb, "replay %d" % r)
+    g.close()
