@@ -95,11 +95,13 @@ __device__ __forceinline__ DomainArgs domain_from(const pw_domain_args& a, const
     return d;
 }
 
-__device__ __forceinline__ int find_domain(const BatchDomain* table, int ndom, int64_t t) {
+// The last row whose `begin` (its first tile or workgroup) is at most t.
+template <typename T>
+__device__ __forceinline__ int find_domain(const BatchDomain* table, int ndom, T t, T BatchDomain::*begin) {
     int lo = 0, hi = ndom - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
-        if (table[mid].tile_begin <= t) lo = mid;
+        if (table[mid].*begin <= t) lo = mid;
         else hi = mid - 1;
     }
     return lo;
@@ -180,7 +182,7 @@ __global__ __launch_bounds__(NT) void pw_batched_kernel(const BatchDomain* __res
         // tiles only move forward: after the first binary search a short
         // forward scan finds the domain (usually zero or one step)
         if (dom < 0) {
-            dom = find_domain(table, ndom, t);
+            dom = find_domain(table, ndom, t, &BatchDomain::tile_begin);
         } else {
             while (dom + 1 < ndom && table[dom + 1].tile_begin <= t) ++dom;
         }
@@ -293,41 +295,46 @@ __device__ __forceinline__ uint32_t lowbias32(uint32_t x) {
 // The (seed, call, domain) key is mixed once by SplitMix64; each element then
 // costs one 32-bit hash of its field and its point index g = k + nz ((j - 1) +
 // ny (i - 1)), so the values do not depend on how the work is split.
-// One workgroup per tile of the plan (the batched kernel's split: a chunk of
-// the (j, k) points of a plane times a segment of x planes), so every
-// workgroup of the grid has work whatever the spread of domain sizes; each
-// thread reads the points of kPerturbPlanes planes before it writes them.
+// One workgroup per chunk of the (j, k) points of a plane times at most
+// `planes` x planes, a split of its own (find_domain by fill_begin): the
+// advection's tiles may be long, and their number too small to fill the chip.
+// Each thread reads the points of kPerturbPlanes planes before it writes them.
 //
-// HALO (the recorded timestep): also the periodic halo of u, v, w, written
-// from the values in hand -- a boundary point's copies go out with it, only
-// w's boundary columns are read besides -- with the result of pw_halo_kernel
-// after this kernel, which would read again what this one has just written.
-// Bound by instruction issue (two 32-bit hashes per element, whose four
-// multiplications run at a quarter of the rate), then by the HBM: 384 domains
-// FP32 386 us with the halo (2.2 GB), against 355 + 84 us and a launch for the
-// counter; addresses advance by additions, and only waves with a boundary
-// column and groups with a boundary plane carry the copies' code (411 us with
-// it in every step).
+// HALO (the recorded timestep): also the periodic halo of u, v, w, with the
+// result of pw_halo_kernel after this kernel.  A thread copies its own points
+// once it has written them: the boundary planes and columns, which are in the
+// cache, are read again, so that only the threads that hold them carry that
+// code, its registers are not needed beside the perturbation's (59-69 in all,
+// seven or eight waves per SIMD; with the copies made from the values in hand
+// 123-135, three or four), and a record may give one array for several fields.
+// Bound by its bytes where a batch exceeds the last-level cache: 384 domains
+// FP64 771 us (4.5 GB, 5.8 TB/s), FP32 366 (6.1 TB/s), int32 367, BF16 268;
+// with the copies in hand and the advection's tiles as its split 773, 377, 743
+// and 362; as perturbation and halo fill one after the other 726 + 102,
+// 351 + 81, 349 + 77 and 223 + 61 and a launch.  20 domains: FP64 37, FP32 22,
+// int32 23, BF16 20 us (37, 24, 40, 26 and 39, 25, 26, 29).
 constexpr int kPerturbPlanes = 4;
 
 template <typename ST, bool HALO>
 __global__ __launch_bounds__(256) void pw_perturb_kernel(const BatchDomain* __restrict__ table, int ndom, int chunk,
-                                                         const pw_domain_args* __restrict__ args, uint64_t seed,
+                                                         int planes, const pw_domain_args* __restrict__ args, uint64_t seed,
                                                          const unsigned long long* __restrict__ call, double amp) {
     using CT = typename compute_of<ST>::type;
-    // HALO: from the last tile to the first, so that the advection after it,
-    // which begins with the first tiles, finds the fields written last in the
-    // last-level cache (and so does the next step's perturbation)
-    const int64_t t = HALO ? (int64_t)(gridDim.x - 1 - blockIdx.x) : (int64_t)blockIdx.x;
-    const BatchDomain b = table[find_domain(table, ndom, t)];
+    // HALO: from the last workgroup's share to the first's, so that the
+    // advection after it, which begins with the first tiles, finds the fields
+    // written last in the last-level cache (and so does the next step's
+    // perturbation)
+    const int t = HALO ? (int)(gridDim.x - 1 - blockIdx.x) : (int)blockIdx.x;
+    const BatchDomain b = table[find_domain(table, ndom, t, &BatchDomain::fill_begin)];
     const int dom = b.rec;   // the caller's domain index keys the hash
     const pw_domain_args& a = args[dom];
     if (!shape_matches(a.shape, b)) return;
-    const int64_t local = t - b.tile_begin;
-    const int c = (int)(local % b.nchunks);
-    const int sg = (int)(local / b.nchunks);
-    const int i0 = 1 + sg * b.seg;                 // <= nx: segments start at or before plane nx
-    const int i1 = min(i0 + b.seg - 1, b.nx);
+    const int local = t - b.fill_begin;
+    const int c = local % b.nchunks;
+    const int sg = local / b.nchunks;
+    const int len = segment_split(b.nx, planes).len;
+    const int i0 = 1 + sg * len;                 // <= nx: segments start at or before plane nx
+    const int i1 = min(i0 + len - 1, b.nx);
     const uint32_t nz = (uint32_t)b.nz, nyz = (uint32_t)b.ny * (uint32_t)b.nz;   // nx ny nz < 2^31 (plan time)
     const uint32_t pend = min((uint32_t)(c + 1) * (uint32_t)chunk, nyz);
     const uint64_t key64 = splitmix64(seed ^ splitmix64((uint64_t)(*call) * 0x100000001b3ull + (uint64_t)dom));
@@ -342,75 +349,81 @@ __global__ __launch_bounds__(256) void pw_perturb_kernel(const BatchDomain* __re
         const float r = (float)(h >> 8) * 0x1.0p-23f - 1.0f;   // [-1, 1)
         return x + static_cast<CT>(amp * (double)r) * sc[q];
     };
-    const bool own_w = a.w != a.u && a.w != a.v;   // else its halo goes out with u's or v's
+    // the planes i0 .. i1 in groups of kPerturbPlanes and a remainder
+    auto by_groups = [&](auto group) {
+        int i = i0;
+        for (; i + kPerturbPlanes - 1 <= i1; i += kPerturbPlanes) group(std::integral_constant<int, kPerturbPlanes>{}, i);
+        static_assert(kPerturbPlanes == 4, "remainders of one to three planes");
+        if (i + 2 == i1) group(std::integral_constant<int, 3>{}, i);
+        else if (i + 1 == i1) group(std::integral_constant<int, 2>{}, i);
+        else if (i == i1) group(std::integral_constant<int, 1>{}, i);
+    };
     for (uint32_t p = (uint32_t)c * (uint32_t)chunk + threadIdx.x; p < pend; p += 256) {
         const uint32_t k = p % nz;
         const uint32_t j = p / nz + 1;
         const int64_t col = k + (int64_t)j * b.sy;
-        // halo columns that copy this one (both may for ny = 1)
-        const bool to_lo = HALO && (int)j == b.ny, to_hi = HALO && j == 1;
-        auto across = [&](global_ptr<U> g, int64_t plane, U x) {   // the row's own halo columns in a plane
-            if (to_lo) g[k + plane] = x;
-            if (to_hi) g[k + (int64_t)(b.ny + 1) * b.sy + plane] = x;
-        };
-        auto spread = [&](global_ptr<U> g, int i, U x) {
-            across(g, (int64_t)i * b.sx, x);
-            if (i == b.nx) {   // plane 0 copies plane nx
-                g[col] = x;
-                across(g, 0, x);
-            }
-            if (i == 1) {      // plane nx + 1 copies plane 1
-                const int64_t plane = (int64_t)(b.nx + 1) * b.sx;
-                g[col + plane] = x;
-                across(g, plane, x);
-            }
-        };
         const int64_t step = b.sx;   // uniform
-        global_ptr<U> at[3];
-#pragma unroll
-        for (int q = 0; q < 3; ++q) at[q] = f[q] + (col + (int64_t)i0 * step);
+        global_ptr<U> at[2] = {f[0] + (col + (int64_t)i0 * step), f[1] + (col + (int64_t)i0 * step)};
         uint32_t n = 2u * ((uint32_t)(i0 - 1) * nyz + p);
-        // N planes from plane i on: all their loads first (unconditional, so
-        // they are in flight together), then the results.  EDGE: with halo copies.
-        auto group = [&](auto count, auto edge, int i) {
+        // N planes: all their loads first (unconditional, so they are in flight
+        // together), then the results
+        auto perturb = [&](auto count, int) {
             constexpr int N = decltype(count)::value;
-            constexpr bool EDGE = decltype(edge)::value;
             CT x[N][2];
-            U w[N];
 #pragma unroll
-            for (int u = 0; u < N; ++u) {
+            for (int u = 0; u < N; ++u)
 #pragma unroll
                 for (int q = 0; q < 2; ++q) x[u][q] = to_compute(from_bits<ST>(at[q][u * step]));
-                if (EDGE) w[u] = at[2][u * step];
-            }
 #pragma unroll
-            for (int u = 0; u < N; ++u) {
+            for (int u = 0; u < N; ++u)
 #pragma unroll
-                for (int q = 0; q < 2; ++q) {
-                    const U y = to_bits(from_compute<ST>(perturbed(x[u][q], n + 2u * (uint32_t)u * nyz + (uint32_t)q, q)));
-                    at[q][u * step] = y;
-                    if (EDGE) spread(f[q], i + u, y);
-                }
-                if (EDGE && own_w) spread(f[2], i + u, w[u]);
-            }
+                for (int q = 0; q < 2; ++q)
+                    at[q][u * step] = to_bits(from_compute<ST>(perturbed(x[u][q], n + 2u * (uint32_t)u * nyz + (uint32_t)q, q)));
 #pragma unroll
-            for (int q = 0; q < 3; ++q) at[q] += N * step;
+            for (int q = 0; q < 2; ++q) at[q] += N * step;
             n += 2u * N * nyz;
         };
-        // waves that hold a boundary column, and groups that hold the first
-        // or the last plane, write halo copies
-        const bool side = HALO && __ballot(to_lo || to_hi) != 0ull;
-        auto run = [&](auto count, int i) {
-            constexpr int N = decltype(count)::value;
-            if (HALO && (side || i == 1 || i + N - 1 == b.nx)) group(count, std::true_type{}, i);
-            else group(count, std::false_type{}, i);
-        };
-        int i = i0;
-        for (; i + kPerturbPlanes - 1 <= i1; i += kPerturbPlanes) run(std::integral_constant<int, kPerturbPlanes>{}, i);
-        static_assert(kPerturbPlanes == 4, "remainders of one to three planes");
-        if (i + 2 == i1) run(std::integral_constant<int, 3>{}, i);
-        else if (i + 1 == i1) run(std::integral_constant<int, 2>{}, i);
-        else if (i == i1) run(std::integral_constant<int, 1>{}, i);
+        by_groups(perturb);
+        if constexpr (HALO) {
+            // halo columns that copy this one (both may for ny = 1)
+            const bool to_lo = (int)j == b.ny, to_hi = j == 1;
+            const int64_t lo = k, hi = k + (int64_t)(b.ny + 1) * b.sy;
+            // this point of plane `from` to plane `to`, and to the halo columns there
+            auto plane_copy = [&](int from, int to) {
+                U x[3];
+#pragma unroll
+                for (int q = 0; q < 3; ++q) x[q] = f[q][col + from * step];
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    f[q][col + to * step] = x[q];
+                    if (to_lo) f[q][lo + to * step] = x[q];
+                    if (to_hi) f[q][hi + to * step] = x[q];
+                }
+            };
+            if (i0 == 1) plane_copy(1, b.nx + 1);
+            if (i1 == b.nx) plane_copy(b.nx, 0);
+            // this column to the halo columns in N planes, all loads first
+            auto column_copy = [&](auto count, int i) {
+                constexpr int N = decltype(count)::value;
+                U x[N][3];
+#pragma unroll
+                for (int u = 0; u < N; ++u)
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) x[u][q] = f[q][col + (i + u) * step];
+#pragma unroll
+                for (int u = 0; u < N; ++u)
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) {
+                        if (to_lo) f[q][lo + (i + u) * step] = x[u][q];
+                        if (to_hi) f[q][hi + (i + u) * step] = x[u][q];
+                    }
+            };
+            if (to_lo || to_hi) {
+                int i = i0;
+                for (; i < i1; i += 2) column_copy(std::integral_constant<int, 2>{}, i);
+                if (i == i1) column_copy(std::integral_constant<int, 1>{}, i);
+            }
+        }
     }
 }
 
@@ -731,6 +744,31 @@ std::vector<int32_t> one_tile_order(const std::vector<BatchDomain>& table, int32
     return order;
 }
 
+// The perturbation's split of a batch (its rows' fill_begin): most planes of a
+// workgroup and, in *fill_tiles, the workgroups; `planes` chunk planes in all.
+// Enough workgroups for two rounds of a full chip (eight workgroups per CU), at
+// least 6 planes (below, finding its domain costs a workgroup more than the
+// balance gains) and at most 10: 6, 10, 16, 24, 40 and 64 planes, recorded
+// timesteps of 60 domains BF16 104, 102, 102, 109, 111, 120 us, int32 151, 152,
+// 155, 157, 162, 174; of 384, FP32 904, 961, 927, 968, 988, 972 (the order
+// changes from run to run), int16 613, 595, 582, 594, 593, 605; of 12, FP64 69,
+// 69, 73, 77, 85, 93.
+int32_t fill_split(std::vector<BatchDomain>& table, int64_t planes, int cus, int64_t* fill_tiles) {
+    int64_t most = std::max<int64_t>(6, std::min<int64_t>(planes / (16 * (int64_t)cus), 10));
+    for (;; most *= 2) {
+        int64_t t = 0;
+        for (const BatchDomain& b : table) t += (int64_t)b.nchunks * segment_split(b.nx, (int32_t)most).n;
+        *fill_tiles = t <= kMaxTiles ? t : 0;
+        if (t <= kMaxTiles || most >= (1 << 30)) break;   // a launch holds them, or none can
+    }
+    int64_t at = 0;
+    for (BatchDomain& b : table) {
+        b.fill_begin = (int32_t)at;
+        at += (int64_t)b.nchunks * segment_split(b.nx, (int32_t)most).n;
+    }
+    return (int32_t)most;
+}
+
 int32_t batched_plan_init(pw_plan* p) {
     BatchState& B = p->batch;
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
@@ -761,15 +799,17 @@ int32_t batched_plan_init(pw_plan* p) {
         std::stable_sort(rows.begin(), rows.end(),
                          [](const BatchDomain& x, const BatchDomain& y) { return x.seg > y.seg; });
     std::vector<BatchDomain>& table = rows;
-    int64_t tiles = 0;
+    int64_t tiles = 0, planes = 0;
     for (BatchDomain& b : table) {
         b.tile_begin = tiles;
         tiles += (int64_t)b.nchunks * b.nseg;
+        planes += (int64_t)b.nchunks * b.nx;
     }
     int dev = 0, cus = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e != hipSuccess) return report_hip(e);
+    B.fill_planes = fill_split(table, planes, cus, &B.fill_tiles);
     std::vector<int32_t> order;
     // The grouped order (one_tile_order) measured 6-11% faster than runs of
     // kOneTileRuns for BF16 and FP16 batches, whose kernels are bound by
@@ -837,17 +877,17 @@ static int32_t launch_advect(const pw_plan* plan, const pw_domain_args* d_args, 
     return e == hipSuccess ? PW_OK : report_hip(e);
 }
 
-// The perturbation of a batch (HALO: and its halo fill), one workgroup per tile.
+// The perturbation of a batch (HALO: and its halo fill).
 template <bool HALO>
 static int32_t launch_perturb(const pw_plan* plan, const pw_domain_args* d_args, uint64_t seed,
                               const unsigned long long* d_call, double amplitude, hipStream_t s) {
-    const Launch& L = plan->batch.launch;
-    if (L.tiles >= (int64_t(1) << 31)) return PW_ERR_UNSUPPORTED;
-    const dim3 grid((unsigned)L.tiles);
-    const BatchDomain* tb = plan->batch.d_table;
-    const int nd = plan->ndomains, ch = L.chunk;
+    const BatchState& B = plan->batch;
+    if (B.fill_tiles == 0) return PW_ERR_UNSUPPORTED;
+    const dim3 grid((unsigned)B.fill_tiles);
+    const BatchDomain* tb = B.d_table;
+    const int nd = plan->ndomains, ch = B.launch.chunk, planes = B.fill_planes;
     auto go = [&](auto kern) {
-        hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, tb, nd, ch, d_args, seed, d_call, amplitude);
+        hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, tb, nd, ch, planes, d_args, seed, d_call, amplitude);
         return hipGetLastError();
     };
     hipError_t e = hipSuccess;

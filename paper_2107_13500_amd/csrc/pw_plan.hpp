@@ -35,7 +35,7 @@ struct BatchDomain {
     int64_t sy, sx;
     int64_t tile_begin;   // first global tile of this domain
     int32_t rec;          // index of the domain's record in the caller's pw_domain_args array
-    int32_t pad_;
+    int32_t fill_begin;   // first workgroup of this domain in the perturbation's own split
 };
 
 struct BatchState {
@@ -44,6 +44,8 @@ struct BatchState {
     unsigned long long* d_errors = nullptr;
     const int32_t* d_order = nullptr;   // one workgroup per tile: each workgroup's tile (-1: none), or NULL
     int device = -1;
+    int32_t fill_planes = 0;     // the perturbation's split: most planes of a workgroup,
+    int64_t fill_tiles = 0;      // and its workgroups (0: more than one launch may hold)
     bool vec_shapes = false;     // every shape allows 16-byte loads
     int32_t kind = 0;            // code paths of the batched kernel (BatchKind in pw_batched.hip)
 };

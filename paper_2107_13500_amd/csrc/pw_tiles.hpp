@@ -34,9 +34,9 @@ struct SegmentSplit {
     int32_t n, len;
 };
 __host__ __device__ inline SegmentSplit segment_split(int32_t nx, int32_t most) {
-    const int64_t m = most < nx ? most : nx;
-    const int64_t n = (nx + m - 1) / m;
-    return SegmentSplit{(int32_t)n, (int32_t)((nx + n - 1) / n)};
+    const uint32_t x = (uint32_t)nx, m = (uint32_t)(most < nx ? most : nx);
+    const uint32_t n = (x + m - 1u) / m;
+    return SegmentSplit{(int32_t)n, (int32_t)((x + n - 1u) / n)};
 }
 
 // Columns of the one-point x-y halo around nx x ny interior columns: up to

@@ -161,3 +161,25 @@ def test_recorded_timestep_where_w_is_also_u_or_v(shared):
         torch.cuda.synchronize()
         assert_same_state(ga, eb, "replay %d" % r)
     g.close()
+
+
+@pytest.mark.parametrize("storage", [B.F64, B.I16], ids=["f64", "i16"])
+@pytest.mark.parametrize("nx,count", [(96, 34), (97, 43), (53, 90)])
+def test_recorded_timestep_of_batches_with_long_perturbation_splits(storage, nx, count):
+    """The perturbation splits a batch by its size, 6 to 10 planes per
+    workgroup: batches whose chunk planes are 8 to 11 times 4096, with
+    groups of four planes and every remainder, against the eager calls (whose
+    noise is checked element by element elsewhere)."""
+    p = inputs.make_problem(nx, 53, 96, 1700)
+    ga, eb = BT.DeviceBatch([p] * count, storage, DEV), BT.DeviceBatch([p] * count, storage, DEV)
+    pa, pb = ga.plan(), eb.plan({"chunk": 256, "seg": 5})   # other chunks and another split
+    g = ga.capture_timestep(pa, seed=29, amplitude=1e-2)
+    for r in range(2):
+        say("long split", B.DTYPE_NAMES[storage], nx, count, r)
+        g.launch()
+        eb.timestep(pb, seed=29, amplitude=1e-2)
+        torch.cuda.synchronize()
+        for d in range(count):
+            for f, (x, y) in enumerate(zip(ga.fields[d], eb.fields[d])):
+                assert torch.equal(x.contiguous().view(torch.uint8), y.contiguous().view(torch.uint8)), (r, d, f)
+    g.close()
