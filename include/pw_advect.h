@@ -347,10 +347,12 @@ int32_t pw_graph_launch(const pw_graph *graph, void *stream);
 /* Free a graph (NULL accepted); no replay of it may still be running. */
 int32_t pw_graph_destroy(pw_graph *graph);
 
-/* Error count of a batched plan (pw_advect_batched, its halo fill and
-   perturbation): the number of domain records skipped so far because their shape did
-   not match the plan, a field pointer was NULL or (vector-aligned plans) not
-   16-byte aligned.  Synchronous (copies one word from the device).  `count`
+/* Error count of a batched plan: the number of domain records that
+   pw_advect_batched has skipped so far (recorded timesteps' advections
+   included) because their shape did not match the plan, a field pointer was
+   NULL, a scale was no power of two or (vector-aligned plans) a pointer was not
+   16-byte aligned.  The halo fill and the perturbation skip records of another
+   shape, or with NULL for a field that they use, without counting them.  Synchronous (copies one word from the device).  `count`
    is a host out-pointer. */
 int32_t pw_plan_error_count(const pw_plan *plan, unsigned long long *count);
 

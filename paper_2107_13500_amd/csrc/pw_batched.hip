@@ -253,7 +253,7 @@ __global__ __launch_bounds__(256) void pw_halo_kernel(const BatchDomain* __restr
                                                       const pw_domain_args* __restrict__ args) {
     const BatchDomain b = table[blockIdx.y];
     const pw_domain_args& a = args[b.rec];
-    if (!shape_matches(a.shape, b)) return;
+    if (!shape_matches(a.shape, b) || !a.u || !a.v || !a.w) return;
     using U = storage_bits<ST>;
     global_ptr<U> f[3] = {as_global((U*)a.u), as_global((U*)a.v), as_global((U*)a.w)};
     const int64_t n = halo_columns(b.nx, b.ny) * b.nz;
@@ -328,7 +328,7 @@ __global__ __launch_bounds__(256) void pw_perturb_kernel(const BatchDomain* __re
     const BatchDomain b = table[find_domain(table, ndom, t, &BatchDomain::fill_begin)];
     const int dom = b.rec;   // the caller's domain index keys the hash
     const pw_domain_args& a = args[dom];
-    if (!shape_matches(a.shape, b)) return;
+    if (!shape_matches(a.shape, b) || !a.u || !a.v) return;
     const int local = t - b.fill_begin;
     const int c = local % b.nchunks;
     const int sg = local / b.nchunks;
@@ -384,7 +384,7 @@ __global__ __launch_bounds__(256) void pw_perturb_kernel(const BatchDomain* __re
             n += 2u * N * nyz;
         };
         by_groups(perturb);
-        if constexpr (HALO) {
+        if (HALO && a.w != nullptr) {   // a record without a field has no halo fill
             // halo columns that copy this one (both may for ny = 1)
             const bool to_lo = (int)j == b.ny, to_hi = j == 1;
             const int64_t lo = k, hi = k + (int64_t)(b.ny + 1) * b.sy;

@@ -420,3 +420,37 @@ def test_default_segments_keep_launches_below_2_to_the_32_threads(storage, shape
     say("long domain", B.DTYPE_NAMES[storage], shape, i)
     assert 0 < i["workgroups"] * i["block"] < 2 ** 32
     assert 0 <= i["batched_workgroups"] * 256 < 2 ** 32
+
+
+@pytest.mark.parametrize("field", [0, 1, 2], ids=["u", "v", "w"])
+@pytest.mark.parametrize("recorded", [False, True], ids=["eager", "recorded"])
+def test_a_record_without_a_field_is_skipped_by_every_part_of_a_timestep(field, recorded):
+    """A NULL u, v or w: no halo is filled and no output written for that
+    domain, nothing is perturbed without u and v, the other domains run as
+    always, and the advection counts the record."""
+    probs = small_problems(SMALL[:4], seed=450)
+    a, b = BT.DeviceBatch(probs, B.F64, DEV), BT.DeviceBatch(probs, B.F64, DEV)
+    rec = B.PwDomainArgs.from_buffer_copy(bytes(a.records[1]))
+    setattr(rec, "uvw"[field], None)
+    a.d_args = B.domain_args_tensor([a.records[0], rec, *a.records[2:]], DEV)
+    before = [t.clone() for t in a.fields[1]]
+    pa, pb = a.plan(), b.plan()
+    say("record without", "uvw"[field], recorded)
+    if recorded:
+        g = a.capture_timestep(pa, seed=31, amplitude=1e-2)
+        g.launch()
+    else:
+        a.timestep(pa, seed=31, amplitude=1e-2)
+    b.timestep(pb, seed=31, amplitude=1e-2)
+    torch.cuda.synchronize()
+    assert pa.error_count() == 1 and int(a.call.item()) == 1
+    for d in (0, 2, 3):
+        for x, y in zip(a.fields[d], b.fields[d]):
+            assert same_bits(x, y)
+    for f, (x, y, z) in enumerate(zip(a.fields[1], before, b.fields[1])):
+        if field == 2 and f < 2:   # u and v are there: perturbed, their halos left
+            assert same_bits(x[1:-1, 1:-1], z[1:-1, 1:-1])
+            for face in (0, -1):
+                assert same_bits(x[face], y[face]) and same_bits(x[:, face], y[:, face])
+        else:
+            assert same_bits(x, y)
