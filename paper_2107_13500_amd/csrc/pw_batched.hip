@@ -531,20 +531,153 @@ int64_t resident_per_cu(int32_t storage, int32_t chunk, int32_t kind, int64_t ld
 // 6 (below, the planes a tile's start reads twice cost more than the balance
 // gains) and at most the length that is best for large batches: 10 planes for
 // FP64 and 12 for FP32, where short tiles keep the uneven domains' streams
-// together in HBM, 64 for the types that convert, whose tiles' start costs
-// more.  Fitted to lengths of 1 .. 96 planes on batches of 5 to 384 domains:
-// on average 1.6% (FP64), 2.7% (FP32), 4% (BF16, int16) and 2.5% (int32) off
-// the best length; fixed lengths of 16 (4- and 8-byte types) and 64 planes are
-// 9%, 13%, 41-47% and 16% off.  384 domains: FP64 1114 -> 1087 us, int32
-// 710 -> 632 us; 13 domains BF16 40 -> 21 us, int16 42 -> 21 us.
-// Without a plan (no longest-first order) the converting types take about half
-// of that: 96 domains BF16 106 us with 32 planes, 112 with 64; 30 domains 43
+// together in HBM.  Fitted to lengths of 1 .. 96 planes on batches of 5 to 384
+// domains: on average 1.6% (FP64) and 2.7% (FP32) off the best length; fixed
+// lengths of 16 planes are 9% and 13% off.  384 domains FP64 1114 -> 1087 us.
+// The types that convert (scheduled_seg with a plan) take 0.7 times the chunk
+// planes per workgroup, at most 48 planes, where nothing orders the tiles by
+// length: 96 domains BF16 106 us with 32 planes, 112 with 64; 30 domains 43
 // with 16, 53 with 64.
-int32_t batched_seg(int32_t storage, int64_t planes, int64_t resident, bool sorted) {
+int32_t batched_seg(int32_t storage, int64_t planes, int64_t resident) {
     const bool wide = storage == PW_F64 || storage == PW_F32;
-    const int64_t most = storage == PW_F64 ? 10 : (wide ? 12 : (sorted ? 64 : 48));
-    const int64_t seg = planes * (wide || sorted ? 13 : 7) / (10 * std::max<int64_t>(1, resident));
+    const int64_t most = storage == PW_F64 ? 10 : (wide ? 12 : 48);
+    const int64_t seg = planes * (wide ? 13 : 7) / (10 * std::max<int64_t>(1, resident));
     return (int32_t)std::max<int64_t>(6, std::min<int64_t>(seg, most));
+}
+
+// Dispatch order of a plan's one-workgroup-per-tile launch.  Each domain's
+// chunks form groups of kOneTileRuns neighbours (they share y-halo columns),
+// and every segment of a group runs on one XCD; the groups are spread over
+// the XCDs by their points, the longest tiles first.  An XCD's queue takes
+// its groups in windows of about as many tiles as the XCD keeps resident
+// and runs segment 0 of every group of the window, then segment 1, and so on
+// -- the march kernel's compact order within each window -- so the tile of
+// segment s + 1 of a group starts as the window's segment-s tiles retire and
+// finds the planes they share still in the XCD's L2.  Workgroups go
+// round-robin over the XCDs: order[k * 8 + x] is the tile of the k-th
+// workgroup of XCD x, -1 past the end of that XCD's queue.
+struct Group {
+    int d, c0, c1;
+};
+std::vector<std::vector<Group>> xcd_groups(const std::vector<BatchDomain>& table) {
+    std::vector<std::vector<Group>> groups(kNumXcd);
+    std::vector<int64_t> load(kNumXcd, 0);
+    for (int d = 0; d < (int)table.size(); ++d) {
+        const BatchDomain& b = table[d];
+        for (int c0 = 0; c0 < b.nchunks; c0 += kOneTileRuns) {
+            const int c1 = std::min(b.nchunks, c0 + kOneTileRuns);
+            const int x = (int)(std::min_element(load.begin(), load.end()) - load.begin());
+            groups[x].push_back(Group{d, c0, c1});
+            load[x] += (int64_t)(c1 - c0) * b.nx;
+        }
+    }
+    return groups;
+}
+// f(group, segment) in an XCD's queue order.
+template <typename F>
+void in_windows(const std::vector<BatchDomain>& table, const std::vector<Group>& gs, int64_t resident_per_xcd, F f) {
+    const size_t window = (size_t)std::max<int64_t>(1, resident_per_xcd / kOneTileRuns);   // groups in flight
+    for (size_t w0 = 0; w0 < gs.size(); w0 += window) {
+        const size_t w1 = std::min(gs.size(), w0 + window);
+        int nseg = 0;
+        for (size_t i = w0; i < w1; ++i) nseg = std::max(nseg, table[gs[i].d].nseg);
+        for (int sg = 0; sg < nseg; ++sg)
+            for (size_t i = w0; i < w1; ++i)
+                if (sg < table[gs[i].d].nseg) f(gs[i], sg);
+    }
+}
+std::vector<int32_t> one_tile_order(const std::vector<BatchDomain>& table, int64_t resident_per_xcd) {
+    const std::vector<std::vector<Group>> groups = xcd_groups(table);
+    std::vector<std::vector<int32_t>> queue(kNumXcd);
+    for (int x = 0; x < kNumXcd; ++x)
+        in_windows(table, groups[x], resident_per_xcd, [&](const Group& g, int sg) {
+            const BatchDomain& b = table[g.d];
+            for (int c = g.c0; c < g.c1; ++c)
+                queue[x].push_back((int32_t)(b.tile_begin + (int64_t)sg * b.nchunks + c));
+        });
+    size_t len = 0;
+    for (const std::vector<int32_t>& q : queue) len = std::max(len, q.size());
+    std::vector<int32_t> order(len * kNumXcd, -1);
+    for (int x = 0; x < kNumXcd; ++x)
+        for (size_t k = 0; k < queue[x].size(); ++k) order[k * kNumXcd + x] = queue[x][k];
+    return order;
+}
+
+// Default segment length of a plan's batch for the types that convert, whose
+// tiles' start costs more, so that longer tiles and the rounds they fill
+// matter: the length with the least predicted time.  The tiles, longest first
+// (`grouped`: in the XCDs' queues), go to the resident workgroups as those come
+// free (a tile of n planes takes n + 3 plane steps); 0.7 of the time are the
+// mean workgroup's steps and 0.3 the last one's, since the chip's rate falls
+// less than the workgroups left.  Lengths: 1.3 times the chunk planes per
+// resident workgroup, and from half to twice the chunk planes.  Measured on 54
+// batches of 10 to 90 domains over all of these lengths: 1.4% (int32), 1.1%
+// (BF16) and 0.7% (int16) off the best length on average; 1.3 times alone, 5%, 8% and 5%, because it fills one and a
+// bit rounds as often as two (30 domains int32 62 us with 49 planes, 50 with
+// 56; 45 domains int16 54 with 64, 50 with 27); one length for every batch (16
+// planes for int32, 64 for the others), 12%, 44% and 47%.  Batches of more than
+// 128 chunk planes per resident workgroup take 64 planes (384 domains int32
+// 632 us, with 16 planes 710).
+int32_t scheduled_seg(const pw_shape* shapes, int32_t n, int32_t chunk, int64_t planes, int64_t resident, bool grouped) {
+    constexpr int64_t kBegin = 3;
+    const int64_t slots = std::max<int64_t>(kNumXcd, resident);
+    if (planes > 128 * slots) return 64;
+    std::vector<BatchDomain> rows(n);
+    std::vector<int64_t> at;   // workgroups that come free at each step
+    size_t now = 0, end = 0;
+    auto begin = [&](int64_t workgroups, int64_t steps, int32_t longest) {
+        // no tile starts after the mean workgroup's end
+        at.assign((size_t)(steps / workgroups + longest + kBegin + 1), 0);
+        at[0] = workgroups;
+        now = 0;
+    };
+    auto run = [&](int64_t tiles, int32_t len) {
+        while (tiles > 0) {
+            while (at[now] == 0) ++now;
+            const int64_t m = std::min(tiles, at[now]);
+            const size_t done = now + (size_t)(len + kBegin);
+            at[now] -= m;
+            at[done] += m;
+            tiles -= m;
+            end = std::max(end, done);
+        }
+    };
+    auto length = [](const BatchDomain& b, int sg) { return sg + 1 < b.nseg ? b.seg : b.nx - b.seg * (b.nseg - 1); };
+    auto predicted = [&](int32_t most) {
+        int64_t steps = 0;
+        for (int32_t d = 0; d < n; ++d) {
+            domain_tiles(shapes[d].nx, shapes[d].ny, shapes[d].nz, chunk, most, &rows[d]);
+            steps += (int64_t)rows[d].nchunks * (rows[d].nx + kBegin * rows[d].nseg);
+        }
+        std::stable_sort(rows.begin(), rows.end(), [](const BatchDomain& x, const BatchDomain& y) { return x.seg > y.seg; });
+        end = 0;
+        if (grouped) {
+            for (const std::vector<Group>& gs : xcd_groups(rows)) {
+                int64_t own = 0;
+                for (const Group& g : gs) own += (int64_t)(g.c1 - g.c0) * (rows[g.d].nx + kBegin * rows[g.d].nseg);
+                begin(slots / kNumXcd, own, most);
+                in_windows(rows, gs, slots / kNumXcd, [&](const Group& g, int sg) { run(g.c1 - g.c0, length(rows[g.d], sg)); });
+            }
+        } else {
+            begin(slots, steps, most);
+            for (const BatchDomain& b : rows) {
+                run((int64_t)b.nchunks * (b.nseg - 1), b.seg);
+                run(b.nchunks, length(b, b.nseg - 1));
+            }
+        }
+        return 0.3 * (double)end + 0.7 * (double)steps / (double)slots;
+    };
+    int32_t best = (int32_t)std::max<int64_t>(6, std::min<int64_t>(planes * 13 / (10 * slots), 64));
+    double least = predicted(best);
+    for (int32_t most = 6; most <= 64; most += std::max(1, most / 8)) {   // .., 16, 18, .., 51, 57, 64
+        if (2 * most * slots < planes || most * slots > 2 * planes) continue;
+        const double t = predicted(most);
+        if (t < least) {
+            least = t;
+            best = most;
+        }
+    }
+    return best;
 }
 
 template <typename ST, int P>
@@ -654,7 +787,11 @@ int32_t batched_launch_shape(int32_t storage, const pw_shape* shapes, int32_t n,
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e != hipSuccess) return report_hip(e);
     int64_t per_cu = resident_per_cu(storage, chunk, k, r.lds_bytes);
-    r.seg = t.seg ? t.seg : batched_seg(storage, planes, (int64_t)cus * std::min<int64_t>(per_cu, 4), sorted);
+    const int64_t resident = (int64_t)cus * std::min<int64_t>(per_cu, 4);
+    r.seg = t.seg ? t.seg
+                  : (sorted && storage != PW_F64 && storage != PW_F32
+                         ? scheduled_seg(shapes, n, chunk, planes, resident, storage == PW_BF16 || storage == PW_F16)
+                         : batched_seg(storage, planes, resident));
     auto count = [&] {
         int64_t tiles = 0;
         for (int32_t d = 0; d < n; ++d) {
@@ -691,57 +828,6 @@ int32_t batched_launch_shape(int32_t storage, const pw_shape* shapes, int32_t n,
     *kind = k;
     *vec_out = vec;
     return PW_OK;
-}
-
-// Dispatch order of a plan's one-workgroup-per-tile launch.  Each domain's
-// chunks form groups of kOneTileRuns neighbours (they share y-halo columns),
-// and every segment of a group runs on one XCD; the groups are spread over
-// the XCDs by their points, the longest tiles first.  An XCD's queue takes
-// its groups in windows of about as many tiles as the XCD keeps resident
-// and runs segment 0 of every group of the window, then segment 1, and so on
-// -- the march kernel's compact order within each window -- so the tile of
-// segment s + 1 of a group starts as the window's segment-s tiles retire and
-// finds the planes they share still in the XCD's L2.  Workgroups go
-// round-robin over the XCDs: order[k * 8 + x] is the tile of the k-th
-// workgroup of XCD x, -1 past the end of that XCD's queue.
-std::vector<int32_t> one_tile_order(const std::vector<BatchDomain>& table, int32_t chunk, int64_t resident_per_xcd) {
-    struct Group {
-        int d, c0, c1;
-    };
-    std::vector<std::vector<Group>> groups(kNumXcd);
-    std::vector<int64_t> load(kNumXcd, 0);
-    for (int d = 0; d < (int)table.size(); ++d) {
-        const BatchDomain& b = table[d];
-        for (int c0 = 0; c0 < b.nchunks; c0 += kOneTileRuns) {
-            const int c1 = std::min(b.nchunks, c0 + kOneTileRuns);
-            const int x = (int)(std::min_element(load.begin(), load.end()) - load.begin());
-            groups[x].push_back(Group{d, c0, c1});
-            load[x] += (int64_t)(c1 - c0) * chunk * b.nx;
-        }
-    }
-    const size_t window = (size_t)std::max<int64_t>(1, resident_per_xcd / kOneTileRuns);   // groups in flight
-    std::vector<std::vector<int32_t>> queue(kNumXcd);
-    for (int x = 0; x < kNumXcd; ++x) {
-        const std::vector<Group>& gs = groups[x];
-        for (size_t w0 = 0; w0 < gs.size(); w0 += window) {
-            const size_t w1 = std::min(gs.size(), w0 + window);
-            int nseg = 0;
-            for (size_t i = w0; i < w1; ++i) nseg = std::max(nseg, table[gs[i].d].nseg);
-            for (int sg = 0; sg < nseg; ++sg)
-                for (size_t i = w0; i < w1; ++i) {
-                    const BatchDomain& b = table[gs[i].d];
-                    if (sg >= b.nseg) continue;
-                    for (int c = gs[i].c0; c < gs[i].c1; ++c)
-                        queue[x].push_back((int32_t)(b.tile_begin + (int64_t)sg * b.nchunks + c));
-                }
-        }
-    }
-    size_t len = 0;
-    for (const std::vector<int32_t>& q : queue) len = std::max(len, q.size());
-    std::vector<int32_t> order(len * kNumXcd, -1);
-    for (int x = 0; x < kNumXcd; ++x)
-        for (size_t k = 0; k < queue[x].size(); ++k) order[k * kNumXcd + x] = queue[x][k];
-    return order;
 }
 
 // The perturbation's split of a batch (its rows' fill_begin): most planes of a
@@ -821,7 +907,7 @@ int32_t batched_plan_init(pw_plan* p) {
         tiles < (int64_t(1) << 31)) {
         // workgroups one XCD keeps resident: its CUs times the occupancy
         const int64_t per_cu = resident_per_cu(p->storage, L.chunk, kind, L.lds_bytes);
-        order = one_tile_order(table, L.chunk, std::max<int64_t>(1, cus / kNumXcd) * per_cu);
+        order = one_tile_order(table, std::max<int64_t>(1, cus / kNumXcd) * per_cu);
         if ((int64_t)order.size() > kMaxTiles) order.clear();   // one long queue: the grid would not fit a launch
         if (!order.empty()) L.workgroups = (int64_t)order.size();
     }
