@@ -118,8 +118,10 @@ typedef struct pw_shape {
               kernel each domain splits its nx planes into n = ceil(nx / seg)
               segments of ceil(nx / n) planes (at most seg; the last may be
               shorter), so a domain's tiles have nearly equal length; the
-              batched default follows the batch's size (6 planes up to 10 for
-              PW_F64, 12 for PW_F32 and 64 for the other types).
+              batched default follows the batch's size: 6 planes up to 10 for
+              PW_F64, 12 for PW_F32 and 64 for the other types (48 without a
+              plan or with a persistent grid), whose length is chosen by the
+              predicted time of the batch's tiles.
    block      threads per workgroup of the direct variant: 64, 128, 256 or 512.
    wg_per_cu  batched launches: 0 (the default) or PW_WG_ONE_PER_TILE runs
               one workgroup per tile, so the hardware hands out the tiles in

@@ -114,7 +114,11 @@ static int32_t even_seg(int32_t nx, int64_t seg) {
 // alone, for every grid, is 17-29% behind: it leaves small grids with too few
 // tiles (64 x 64 x 64 FP64: 32 tiles, 16.9 us; 256 tiles, 5.9 us) and ragged
 // ones with long tiles out of step (1100 x 1000 x 64 FP32: 2.07 rounds of 65
-// planes, 387 us; 7.9 rounds of 17, 318 us).
+// planes, 387 us; 7.9 rounds of 17, 318 us).  The resident tiles are those of
+// the compiled heights' kernels; the class kernels of FP32 and int32 for any
+// height above 84 keep fewer (three and one per CU), and only FP64 has
+// constants of its own for the classes, so their segments may be some percent
+// off the best.
 struct SegModel {
     int32_t planes;   // best segment length with many tiles
     double begin;     // a tile's start with many tiles, in plane steps
@@ -211,14 +215,12 @@ int32_t resolve_launch(int32_t storage, const pw_shape& s, const pw_tuning& t, L
         if (r.lds_bytes > kMaxDynamicLds) return PW_ERR_UNSUPPORTED;
         r.seg = t.seg ? std::min(t.seg, s.nx) : auto_seg(storage, s, r.nchunks, r.lds_bytes);
         r.nseg = (s.nx + r.seg - 1) / r.seg;
-        r.tiles = (int64_t)r.nchunks * r.nseg;
     } else {
         const int32_t block = t.block ? t.block : direct_block(storage, s);
         if (block != 64 && block != 128 && block != 256 && block != 512) return PW_ERR_INVALID_ARG;
         if (s.nx > 65535) return PW_ERR_INVALID_ARG;
         r.block = block;
         r.chunk = 0;
-        r.seg = 1;
         const int64_t pairs = s.ny * (((int64_t)s.nz + 1) / 2);   // a lane takes two levels
         const int64_t per = block / 64 * kDirectPairs;
         r.nchunks = (int32_t)((pairs + per - 1) / per);

@@ -307,12 +307,14 @@ __device__ __forceinline__ uint32_t lowbias32(uint32_t x) {
 // code, its registers are not needed beside the perturbation's (59-69 in all,
 // seven or eight waves per SIMD; with the copies made from the values in hand
 // 123-135, three or four), and a record may give one array for several fields.
-// Bound by its bytes where a batch exceeds the last-level cache: 384 domains
-// FP64 771 us (4.5 GB, 5.8 TB/s), FP32 366 (6.1 TB/s), int32 367, BF16 268;
-// with the copies in hand and the advection's tiles as its split 773, 377, 743
-// and 362; as perturbation and halo fill one after the other 726 + 102,
-// 351 + 81, 349 + 77 and 223 + 61 and a launch.  20 domains: FP64 37, FP32 22,
-// int32 23, BF16 20 us (37, 24, 40, 26 and 39, 25, 26, 29).
+// Bound by the HBM for 4- and 8-byte storage and by instruction issue (two
+// 32-bit hashes per element, whose four multiplications run at a quarter of the
+// rate) for the 16-bit types: 384 domains FP64 771 us (4.5 GB, 5.8 TB/s), FP32
+// 366 (VALU busy 0.53), int32 367, BF16 268 (1.05 GB, VALU busy 0.83); with the
+// copies in hand and the advection's tiles as its split 773, 377, 743 and 362;
+// as perturbation and halo fill one after the other 726 + 102, 351 + 81, 349 +
+// 77 and 223 + 61 and a launch.  20 domains: FP64 37, FP32 22, int32 23, BF16
+// 20 us (37, 24, 40, 26 and 39, 25, 26, 29).
 constexpr int kPerturbPlanes = 4;
 
 template <typename ST, bool HALO>

@@ -874,9 +874,10 @@ struct MarchTile {
     // CARRY: this step's blocks of pair pq, from the carried registers where
     // the previous step read them, else from LDS (slots sm, sc, sp hold planes
     // i-1, i, i+1).  Compile-time loop over all 81 keys; unused keys vanish.
-    // Each LDS read is a single 8-byte read at an immediate offset from the
-    // pair's one base address (every slot, field and row lies within the
-    // 64 KiB offset range).  A scheduling barrier after each read keeps the
+    // Each LDS read is a single read (8 bytes for FP32 compute, 16 for FP64) at
+    // an immediate offset from the pair's base address -- one with a compiled
+    // height, one per row otherwise; every slot and field lies within the
+    // 64 KiB offset range.  A scheduling barrier after each read keeps the
     // compiler from pairing reads into two-address reads, whose 2 KiB offset
     // range would cost a vector add for a new base address nearly every
     // time: in these VALU-bound kernels five such adds per plane and thread

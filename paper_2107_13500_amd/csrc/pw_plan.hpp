@@ -15,12 +15,12 @@ namespace pw {
 struct Launch {
     int32_t variant = 0;
     int32_t chunk = 0;     // march: points per workgroup chunk
-    int32_t seg = 0;       // march: planes per segment
+    int32_t seg = 0;       // planes per segment
     int32_t block = 0;     // threads per workgroup
-    int32_t nchunks = 0;   // march: chunks per plane; direct: blocks per plane
-    int32_t nseg = 0;      // march: segments; direct: planes
-    int32_t run = 0;       // march: compact tile order, neighbouring tiles per XCD and block (0: not used)
-    int32_t blocks = 0;    // march: compact tile order, full blocks of tiles
+    int32_t nchunks = 0;   // chunks per plane (direct: workgroups' shares of its pairs)
+    int32_t nseg = 0;      // segments
+    int32_t run = 0;       // compact tile order, neighbouring tiles per XCD and block (0: not used)
+    int32_t blocks = 0;    // compact tile order, full blocks of tiles
     int64_t workgroups = 0;
     int64_t tiles = 0;
     int64_t lds_bytes = 0;
@@ -39,7 +39,7 @@ struct BatchDomain {
 };
 
 struct BatchState {
-    Launch launch;               // shared kernel shape (chunk, seg, wpad for the largest nz)
+    Launch launch;               // shared kernel shape (chunk, bound of the segments, LDS)
     BatchDomain* d_table = nullptr;
     unsigned long long* d_errors = nullptr;
     const int32_t* d_order = nullptr;   // one workgroup per tile: each workgroup's tile (-1: none), or NULL
