@@ -296,15 +296,18 @@ def fields_fit(plan: Plan, fields, tz) -> bool:
         layout = plan._layout = (torch_dtype(plan.storage), (nx + 2, ny + 2, nz), (sx, sy, 1), nz,
                                  _torch().float64)
     dtype, size, strides, nz, f64 = layout
-    dev = fields[0].get_device()
-    if not fields[0].is_cuda:
+    try:
+        dev = fields[0].get_device()
+        if not fields[0].is_cuda:
+            return False
+        for t in fields:
+            if t.dtype is not dtype or t.shape != size or t.stride() != strides or t.get_device() != dev:
+                return False
+        for t in tz:
+            if t.dtype is not f64 or t.numel() < nz or not t.is_contiguous() or t.get_device() != dev:
+                return False
+    except (AttributeError, RuntimeError, TypeError):   # no tensor, or one without strides
         return False
-    for t in fields:
-        if t.dtype is not dtype or t.shape != size or t.stride() != strides or t.get_device() != dev:
-            return False
-    for t in tz:
-        if t.dtype is not f64 or t.numel() < nz or not t.is_contiguous() or t.get_device() != dev:
-            return False
     return True
 
 

@@ -96,3 +96,21 @@ def test_the_quick_check_refuses_whatever_check_fields_refuses():
         assert not B.fields_fit(FakePlan(), good[0], z)
     host = [OnDevice(t, dev=-1) for t in fields()], [OnDevice(t, dev=-1) for t in coefs()]
     assert not B.fields_fit(FakePlan(), *host)
+
+
+def test_the_quick_check_leaves_host_arrays_and_layouts_without_strides_to_the_naming_check():
+    """What is no tensor of plain strides gets check_fields' own error, not one
+    from a query that it lacks."""
+    import numpy as np
+    good = [OnDevice(t) for t in fields()], [OnDevice(t) for t in coefs()]
+    for odd in (np.zeros((8, 7, 8)), None, torch.zeros(8, 7, 8, dtype=torch.float64).to_sparse()):
+        for i in range(6):
+            f = list(good[0])
+            f[i] = odd
+            assert not B.fields_fit(FakePlan(), f, good[1])
+        for i in range(4):
+            z = list(good[1])
+            z[i] = odd
+            assert not B.fields_fit(FakePlan(), good[0], z)
+    with pytest.raises(ValueError, match="dtype"):
+        B.check_fields(B.F64, SHAPE, [np.zeros((8, 7, 8))] * 6, coefs())
