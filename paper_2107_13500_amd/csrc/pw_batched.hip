@@ -836,11 +836,10 @@ int32_t batched_launch_shape(int32_t storage, const pw_shape* shapes, int32_t n,
 // workgroup and, in *fill_tiles, the workgroups; `planes` chunk planes in all.
 // Enough workgroups for two rounds of a full chip (eight workgroups per CU), at
 // least 6 planes (below, finding its domain costs a workgroup more than the
-// balance gains) and at most 10: 6, 10, 16, 24, 40 and 64 planes, recorded
-// timesteps of 60 domains BF16 104, 102, 102, 109, 111, 120 us, int32 151, 152,
-// 155, 157, 162, 174; of 384, FP32 904, 961, 927, 968, 988, 972 (the order
-// changes from run to run), int16 613, 595, 582, 594, 593, 605; of 12, FP64 69,
-// 69, 73, 77, 85, 93.
+// balance gains) and at most 10.  With 6, 10, 16, 24, 40 and 64 planes, recorded
+// timesteps of 12 domains FP64 68, 69, 71, 74, 79, 85 us; of 60 domains BF16 97,
+// 96, 97, 100, 104, 112, int32 145, 145, 146, 147, 154, 164; of 384, FP32 947,
+// 953, 959, 965, 974, 983, int16 606, 585, 577, 575, 582, 601.
 int32_t fill_split(std::vector<BatchDomain>& table, int64_t planes, int cus, int64_t* fill_tiles) {
     int64_t most = std::max<int64_t>(6, std::min<int64_t>(planes / (16 * (int64_t)cus), 10));
     for (;; most *= 2) {
